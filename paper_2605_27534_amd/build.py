@@ -1,36 +1,55 @@
 """Builds libsurf.so (the HIP library behind include/surf.h) in-tree for gfx950.
 
     python -m paper_2605_27534_amd.build
+
+The kernel families with many instances are translation units of their own,
+compiled once per precision; all units compile in parallel.
 """
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsurf.so")
-SOURCES = [os.path.join(CSRC, "surf_api.hip")]
-HEADERS = [os.path.join(CSRC, f) for f in ("surf_common.hpp", "surf_kernels.hpp")] + [
-    os.path.join(ROOT, "include", "surf.h")]
+PER_PRECISION = ["surf_col2d.hip", "surf_batch_col2d.hip", "surf_col3d.hip", "surf_hj.hip"]
+UNITS = [("surf_api.hip", None)] + [(f, r) for r in ("float", "double") for f in PER_PRECISION]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
-    "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
+    "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     # packed FP32 instructions stay off: ordinary float code only
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
 
 
-def build(verbose: bool = False) -> str:
-    tmp = LIB + ".tmp%d" % os.getpid()
-    cmd = [HIPCC, *FLAGS, "-o", tmp, *SOURCES]
+def _compile(unit, out, verbose):
+    src, real = unit
+    obj = os.path.join(out, "%s_%s.o" % (src[:-4], real))
+    cmd = [HIPCC, *FLAGS, "-c", "-o", obj, os.path.join(CSRC, src)]
+    if real:
+        cmd.insert(-3, "-DSURF_REAL=" + real)
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
+    return obj
+
+
+def build(verbose: bool = False) -> str:
+    tmp = LIB + ".tmp%d" % os.getpid()
+    with tempfile.TemporaryDirectory() as out:
+        with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as pool:
+            objs = list(pool.map(lambda u: _compile(u, out, verbose), UNITS))
+        cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp, *objs]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.check_call(cmd)
     os.replace(tmp, LIB)
     return LIB
 

@@ -2,6 +2,7 @@
 // checks, workspace carving and kernel launches on the caller's stream.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -17,6 +18,7 @@
 #include "surf_kernels.hpp"
 #include "surf_step2d.hpp"
 #include "surf_col2d.hpp"
+#include "surf_hj.hpp"
 #include "surf_col3d.hpp"
 #include "surf_geo3d.hpp"
 #include "surf_adjoint.hpp"
@@ -25,6 +27,7 @@
 #include "surf_acdi.hpp"
 #include "surf_capillary.hpp"
 #include "surf_capillary3d.hpp"
+#include "surf_launch.hpp"
 
 using namespace surf;
 
@@ -284,7 +287,6 @@ int ntiles_2d(const surf_grid* gr, int* t) {
 // COL_OUT columns, row chunks of COL_TY rows (FP32) or COL_TY64 (FP64),
 // COL_WAVES chunks per workgroup.  Returns the workgroup count (0 when the
 // kernel does not apply).
-constexpr int COL_TY = 8, COL_TY64 = 8;
 int col_shape(const surf_grid* gr, const surf_params* p, int* strips, int* groups) {
   *strips = *groups = 0;
   if (gr->dim != 2 || p->flux_form != SURF_FLUX_WEIGHTED) return 0;
@@ -302,7 +304,6 @@ int col_shape(const surf_grid* gr, const surf_params* p, int* strips, int* group
 // COL_OUT columns, blocks of C3_OUT_ROWS rows, chunks of C3_TZ planes (FP32)
 // or C3_TZ64 (FP64).  Returns the workgroup count (0 when the kernel does not
 // apply).
-constexpr int C3_TZ = 16, C3_TZ64 = 8;
 
 // the 3D pipelined moving interface keeps a third level-set buffer
 bool snapshot_needed(const surf_grid* gr, const surf_params* p, int nc3) {
@@ -426,28 +427,67 @@ void acdi_init(surf_ctx* c) {
                      make_par<R>(c), (const R*)c->chi[c->chi_cur], (R*)c->acdi[0], n);
 }
 
+// Pin data and `iters` sweeps of the whole box (full: from chi0).  Several
+// sweeps run per launch, with as many launches, modulo 2, as sweeps, so that
+// the result is in the buffer the sweep count alone determines.
 template <typename R>
 int geometry_impl(surf_ctx* c, const void* vof, int full) {
-  Par<R> p = make_par<R>(c);
-  long long n = c->ncell;
+  const bool three = c->grid.dim == 3;
   const R* f = (const R*)vof;
   if (!full) materialize<R>(c);
-  hipLaunchKernelGGL(k_pin<R>, dim3(grid1d(n)), dim3(BLOCK), 0, c->stream, c->g, p, f,
-                     (R*)c->g0, n);
-  int iters;
-  if (full) {
-    hipLaunchKernelGGL(k_chi0<R>, dim3(grid1d(n)), dim3(BLOCK), 0, c->stream, c->g, p, f,
-                       (R*)c->chi[c->chi_cur], n);
-    iters = hj_init_iters(c);
-  } else {
-    iters = c->prm.hj_iters_step;
+  HjArgs<R> a{};
+  a.g = c->g;
+  a.p = make_par<R>(c);
+  a.g0 = (const R*)c->g0;
+  a.dtau = (R)(c->grid.h / c->grid.dim);
+  const int* n = c->g.n;
+  const dim3 pg((n[0] + PIN_TX - 1) / PIN_TX, std::min((n[1] + PIN_TY - 1) / PIN_TY, 65535),
+                std::min(n[2], 65535));
+  R* chi0 = full ? (R*)c->chi[c->chi_cur] : nullptr;
+  launch_pin<R>(c->stream, pg, c->g, a.p, f, (R*)c->g0, chi0);
+  const int iters = full ? hj_init_iters(c) : c->prm.hj_iters_step;
+  // the flags of the 3D blocks (two arrays of two numbers each) live in the
+  // reduction records, free outside a step: an 80-byte record stands for a
+  // tile of 16x8x8 (FP32) or 8x8x4 (FP64) cells, at most four or two blocks
+  R* fl[2] = {nullptr, nullptr};
+  if (three) {
+    a.strips = (n[0] + HJ3_X - 1) / HJ3_X;
+    a.yblocks = (n[1] + HJ3_Y - 1) / HJ3_Y;
+    a.zblocks = (n[2] + HJ3_Z - 1) / HJ3_Z;
+    a.per_xcd = a.strips * ((a.yblocks + 3) / 4) * ((a.zblocks + 7) / 8);
+    const long long nb = (long long)a.strips * a.yblocks * a.zblocks;
+    fl[0] = (R*)c->part;
+    fl[1] = fl[0] + 2 * nb;
+    // a wrapped halo of two cells must not reach past a neighbour block
+    const int edge[3] = {HJ3_X, HJ3_Y, HJ3_Z};
+    a.skip = 1;
+    for (int d = 0; d < 3; ++d)
+      if (c->g.bc[d][0] == BC_PERIODIC && n[d] % edge[d] == 1) a.skip = 0;
   }
-  R dtau = (R)(c->grid.h / c->grid.dim);
-  for (int it = 0; it < iters; ++it) {
-    int nxt = 1 - c->chi_cur;
+  const int S = three ? 2 : 4;
+  const int many = iters / S / 2 * 2;  // launches of S sweeps; the rest run one by one
+  int cur = 0;
+  for (int it = 0, k = 0; it < iters; ++k) {
+    const bool m = k < many;
+    const int nxt = 1 - c->chi_cur;
+    a.src = (const R*)c->chi[c->chi_cur];
+    a.dst = (R*)c->chi[nxt];
+    a.fl_in = fl[cur];
+    a.fl_out = fl[1 - cur];
+    a.fl_init = fl[cur];
     Timed tm(c, 1);
-    hipLaunchKernelGGL(k_hj<R>, dim3(grid1d(n)), dim3(BLOCK), 0, c->stream, c->g, p,
-                       (const R*)c->chi[c->chi_cur], (const R*)c->g0, (R*)c->chi[nxt], dtau, n);
+    if (three) {
+      launch_hj3<R>(c->stream, m, k == 0, a);
+    } else {
+      const int out = 64 - 2 * (m ? 4 : 1);
+      a.strips = (n[0] + out - 1) / out;
+      a.yblocks = (n[1] + HJ2_TY - 1) / HJ2_TY;
+      a.nwg = a.strips * ((a.yblocks + 3) / 4);
+      a.per_xcd = (a.nwg + 7) / 8;
+      launch_hj2<R>(c->stream, m, a);
+    }
+    it += m ? S : 1;
+    cur = 1 - cur;
     c->chi_cur = nxt;
   }
   c->has_chi = true;
@@ -569,66 +609,6 @@ bool geom2d_ok(const surf_ctx* c) {
   if (K > 16) return false;
   int KH = K <= 8 ? 8 : 16;
   return c->grid.n[0] >= 2 * (KH + 2) && c->grid.n[1] >= 2 * (KH + 2);
-}
-
-template <typename R, int TY>
-void launch_col2d(surf_ctx* c, const ColArgs<R>& a, bool has_u, bool bulk) {
-  const dim3 grid(8 * a.per_xcd), block(64 * COL_WAVES);
-  if (c->grid.axisym) {
-    if (has_u && (c->prm.limiter || c->prm.transverse)) {
-      // substep-1 variants on the rings: Cartesian face values, ring weights
-      const int v = (c->prm.limiter ? 1 : 0) + (c->prm.transverse ? 2 : 0);
-      if (bulk) {
-        if (v == 1) hipLaunchKernelGGL((k_col2d<R, TY, true, true, true, 1, false>), grid, block, 0, c->stream, a);
-        else if (v == 2) hipLaunchKernelGGL((k_col2d<R, TY, true, true, true, 0, true>), grid, block, 0, c->stream, a);
-        else hipLaunchKernelGGL((k_col2d<R, TY, true, true, true, 1, true>), grid, block, 0, c->stream, a);
-      } else {
-        if (v == 1) hipLaunchKernelGGL((k_col2d<R, TY, true, false, true, 1, false>), grid, block, 0, c->stream, a);
-        else if (v == 2) hipLaunchKernelGGL((k_col2d<R, TY, true, false, true, 0, true>), grid, block, 0, c->stream, a);
-        else hipLaunchKernelGGL((k_col2d<R, TY, true, false, true, 1, true>), grid, block, 0, c->stream, a);
-      }
-      return;
-    }
-    if (has_u && bulk) hipLaunchKernelGGL((k_col2d<R, TY, true, true, true>), grid, block, 0, c->stream, a);
-    else if (has_u) hipLaunchKernelGGL((k_col2d<R, TY, true, false, true>), grid, block, 0, c->stream, a);
-    else if (bulk) hipLaunchKernelGGL((k_col2d<R, TY, false, true, true>), grid, block, 0, c->stream, a);
-    else hipLaunchKernelGGL((k_col2d<R, TY, false, false, true>), grid, block, 0, c->stream, a);
-    return;
-  }
-  if (has_u && (c->prm.limiter || c->prm.transverse)) {
-    // substep-1 variants (the scheme only matters with a flow)
-    const int v = (c->prm.limiter ? 1 : 0) + (c->prm.transverse ? 2 : 0);
-    if (bulk) {
-      if (v == 1) hipLaunchKernelGGL((k_col2d<R, TY, true, true, false, 1, false>), grid, block, 0, c->stream, a);
-      else if (v == 2) hipLaunchKernelGGL((k_col2d<R, TY, true, true, false, 0, true>), grid, block, 0, c->stream, a);
-      else hipLaunchKernelGGL((k_col2d<R, TY, true, true, false, 1, true>), grid, block, 0, c->stream, a);
-    } else {
-      if (v == 1) hipLaunchKernelGGL((k_col2d<R, TY, true, false, false, 1, false>), grid, block, 0, c->stream, a);
-      else if (v == 2) hipLaunchKernelGGL((k_col2d<R, TY, true, false, false, 0, true>), grid, block, 0, c->stream, a);
-      else hipLaunchKernelGGL((k_col2d<R, TY, true, false, false, 1, true>), grid, block, 0, c->stream, a);
-    }
-    return;
-  }
-  if (has_u && bulk) hipLaunchKernelGGL((k_col2d<R, TY, true, true>), grid, block, 0, c->stream, a);
-  else if (has_u) hipLaunchKernelGGL((k_col2d<R, TY, true, false>), grid, block, 0, c->stream, a);
-  else if (bulk) hipLaunchKernelGGL((k_col2d<R, TY, false, true>), grid, block, 0, c->stream, a);
-  else hipLaunchKernelGGL((k_col2d<R, TY, false, false>), grid, block, 0, c->stream, a);
-}
-
-template <typename R, int TZ>
-void launch_col3d(surf_ctx* c, const Col3Args<R>& a, bool has_u, bool bulk) {
-  const dim3 grid(8 * a.per_xcd), block(64 * C3_WAVES);
-  if (a.Pst) {  // the instance that also stores the advected state
-    if (has_u && bulk) hipLaunchKernelGGL((k_col3d<R, TZ, true, true, true>), grid, block, 0, c->stream, a);
-    else if (has_u) hipLaunchKernelGGL((k_col3d<R, TZ, true, false, true>), grid, block, 0, c->stream, a);
-    else if (bulk) hipLaunchKernelGGL((k_col3d<R, TZ, false, true, true>), grid, block, 0, c->stream, a);
-    else hipLaunchKernelGGL((k_col3d<R, TZ, false, false, true>), grid, block, 0, c->stream, a);
-    return;
-  }
-  if (has_u && bulk) hipLaunchKernelGGL((k_col3d<R, TZ, true, true, false>), grid, block, 0, c->stream, a);
-  else if (has_u) hipLaunchKernelGGL((k_col3d<R, TZ, true, false, false>), grid, block, 0, c->stream, a);
-  else if (bulk) hipLaunchKernelGGL((k_col3d<R, TZ, false, true, false>), grid, block, 0, c->stream, a);
-  else hipLaunchKernelGGL((k_col3d<R, TZ, false, false, false>), grid, block, 0, c->stream, a);
 }
 
 template <typename R, int KH>
@@ -753,8 +733,8 @@ void col2d_transport(surf_ctx* c, const void* const* u, const void* F_in, const 
   a.groups = c->col_groups;
   a.nwg = c->col_nwg;
   a.per_xcd = (c->col_nwg + 7) / 8;
-  if constexpr (sizeof(R) == 4) launch_col2d<R, COL_TY>(c, a, has_u, bulk);
-  else launch_col2d<R, COL_TY64>(c, a, has_u, bulk);
+  const int variant = (c->prm.limiter ? 1 : 0) + (c->prm.transverse ? 2 : 0);
+  launch_col2d<R>(c->stream, c->grid.axisym != 0, variant, a, has_u, bulk);
 }
 
 // The 3D weighted-form transport kernel alone, on the context's stream.
@@ -785,8 +765,7 @@ void col3d_transport(surf_ctx* c, const void* const* u, const void* F_in, const 
   a.per_xcd = (c->c3_nwg + 7) / 8;
   a.Fst = (R*)F_star;
   a.Pst = (R*)psi_star;
-  if constexpr (sizeof(R) == 4) launch_col3d<R, C3_TZ>(c, a, has_u, bulk);
-  else launch_col3d<R, C3_TZ64>(c, a, has_u, bulk);
+  launch_col3d<R>(c->stream, a, has_u, bulk);
 }
 
 // Weighted-form moving geometry in 2D on `st`: the classify pass, then the
@@ -2343,21 +2322,8 @@ void batch_launch_col(surf_batch* b, int ty, int grid, int parity) {
   const ColArgs<R>* inst = (const ColArgs<R>*)b->col_inst;
   const int2* queue = (const int2*)b->col_queue;
   const int* first = (const int*)b->first;
-  const dim3 gr(grid), bl(64 * COL_WAVES);
-  if (rings) {
-    if (ty == 16)
-      hipLaunchKernelGGL((k_batch_col2d<R, 16, true>), gr, bl, 0, b->stream, inst, queue,
-                         b->ncol_q, first, parity, b->part);
-    else
-      hipLaunchKernelGGL((k_batch_col2d<R, 8, true>), gr, bl, 0, b->stream, inst, queue,
-                         b->ncol_q, first, parity, b->part);
-  } else if (ty == 16) {
-    hipLaunchKernelGGL((k_batch_col2d<R, 16>), gr, bl, 0, b->stream, inst, queue, b->ncol_q,
-                       first, parity, b->part);
-  } else {
-    hipLaunchKernelGGL((k_batch_col2d<R, 8>), gr, bl, 0, b->stream, inst, queue, b->ncol_q,
-                       first, parity, b->part);
-  }
+  launch_batch_col2d<R>(b->stream, ty, rings, grid, inst, queue, b->ncol_q, first, parity,
+                        b->part);
 }
 
 template <typename R>

@@ -1,0 +1,37 @@
+// surf_hj.hip -- launchers of the whole-box redistancing, compiled once per
+// precision (SURF_REAL).
+#include "surf_launch.hpp"
+
+namespace surf {
+
+template <typename R>
+void launch_pin(hipStream_t st, dim3 grid, const Grid& g, const Par<R>& p, const R* vof, R* g0,
+                R* chi) {
+  if (g.dim == 3)
+    hipLaunchKernelGGL((k_pin<R, 3>), grid, dim3(PIN_TX * PIN_TY), 0, st, g, p, vof, g0, chi);
+  else
+    hipLaunchKernelGGL((k_pin<R, 2>), grid, dim3(PIN_TX * PIN_TY), 0, st, g, p, vof, g0, chi);
+}
+
+template <typename R>
+void launch_hj2(hipStream_t st, bool many, const HjArgs<R>& a) {
+  const dim3 grid(8 * a.per_xcd), block(256);
+  if (many) hipLaunchKernelGGL((k_hj2<R, 4>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_hj2<R, 1>), grid, block, 0, st, a);
+}
+
+template <typename R>
+void launch_hj3(hipStream_t st, bool many, bool first, const HjArgs<R>& a) {
+  const dim3 grid(8 * a.per_xcd), block(256);
+  if (many && first) hipLaunchKernelGGL((k_hj3<R, 2, true>), grid, block, 0, st, a);
+  else if (many) hipLaunchKernelGGL((k_hj3<R, 2, false>), grid, block, 0, st, a);
+  else if (first) hipLaunchKernelGGL((k_hj3<R, 1, true>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_hj3<R, 1, false>), grid, block, 0, st, a);
+}
+
+template void launch_pin<SURF_REAL>(hipStream_t, dim3, const Grid&, const Par<SURF_REAL>&,
+                                    const SURF_REAL*, SURF_REAL*, SURF_REAL*);
+template void launch_hj2<SURF_REAL>(hipStream_t, bool, const HjArgs<SURF_REAL>&);
+template void launch_hj3<SURF_REAL>(hipStream_t, bool, bool, const HjArgs<SURF_REAL>&);
+
+}  // namespace surf

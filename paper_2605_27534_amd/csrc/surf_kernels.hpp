@@ -1,8 +1,5 @@
 // surf_kernels.hpp -- HIP kernels of libsurf for gfx950.
 //
-//   k_pin      VoF -> redistancing pin data (section 2.5)
-//   k_chi0     initial level set chi0 = (f - 1/2) h
-//   k_hj       one Godunov Hamilton-Jacobi sweep (section 2.5)
 //   k_step     the fused transport step: advection (section 3.1 substep 1),
 //              confinement + diffusion + exchange (substep 2, sections 2.6,
 //              3.2, Appendices A and C), equation of state (sections 2.3, 5,
@@ -16,89 +13,6 @@
 namespace surf {
 
 constexpr int BLOCK = 256;
-
-// ---------------------------------------------------------------- geometry
-template <typename R>
-__global__ void __launch_bounds__(BLOCK) k_chi0(Grid g, Par<R> p, const R* __restrict__ vof,
-                                                R* __restrict__ chi, long long ncell) {
-  long long c = (long long)blockIdx.x * BLOCK + threadIdx.x;
-  if (c >= ncell) return;
-  chi[c] = (vof[c] - R(0.5)) * p.h;
-}
-
-// Pin data: cells whose face neighbour has chi0 of the opposite (or zero)
-// sign are pinned to the subcell distance h chi0 / Delta (Russo-Smereka);
-// the others carry only the sign of chi0, stored as +-infinity.
-template <typename R>
-__global__ void __launch_bounds__(BLOCK) k_pin(Grid g, Par<R> p, const R* __restrict__ vof,
-                                               R* __restrict__ g0, long long ncell) {
-  long long c = (long long)blockIdx.x * BLOCK + threadIdx.x;
-  if (c >= ncell) return;
-  int i = (int)(c % g.n[0]);
-  int j = (int)((c / g.n[0]) % g.n[1]);
-  int k = (int)(c / ((long long)g.n[0] * g.n[1]));
-  int xyz[3] = {i, j, k};
-  R x0 = (vof[c] - R(0.5)) * p.h;
-  bool cut = false;
-  R jump = R(0), grad2 = R(0);
-  for (int d = 0; d < g.dim; ++d) {
-    int a[3] = {i, j, k}, b[3] = {i, j, k};
-    a[d] = map_axis(xyz[d] - 1, g.n[d], g.bc[d][0], g.bc[d][1]);
-    b[d] = map_axis(xyz[d] + 1, g.n[d], g.bc[d][0], g.bc[d][1]);
-    R xm = (vof[cell_index(g, a[0], a[1], a[2])] - R(0.5)) * p.h;
-    R xp = (vof[cell_index(g, b[0], b[1], b[2])] - R(0.5)) * p.h;
-    cut = cut || (x0 * xm <= R(0)) || (x0 * xp <= R(0));
-    jump = fmax(jump, fabs(xm - x0));
-    jump = fmax(jump, fabs(xp - x0));
-    R cd = R(0.5) * (xp - xm);
-    grad2 += cd * cd;
-  }
-  R Delta = fmax(fmax(rsqrt_<R>(grad2), jump), R(1e-30) * p.h);
-  R inf = R(INFINITY);
-  g0[c] = cut ? p.h * x0 / Delta : (x0 > R(0) ? inf : -inf);
-}
-
-template <typename R>
-__global__ void __launch_bounds__(BLOCK) k_hj(Grid g, Par<R> p, const R* __restrict__ src,
-                                              const R* __restrict__ g0, R* __restrict__ dst,
-                                              R dtau, long long ncell) {
-  long long c = (long long)blockIdx.x * BLOCK + threadIdx.x;
-  if (c >= ncell) return;
-  R gv = g0[c];
-  R v;
-  if (fabs(gv) < R(INFINITY)) {
-    v = gv;
-  } else {
-    int i = (int)(c % g.n[0]);
-    int j = (int)((c / g.n[0]) % g.n[1]);
-    int k = (int)(c / ((long long)g.n[0] * g.n[1]));
-    int xyz[3] = {i, j, k};
-    R x = src[c];
-    R G2 = R(0);
-    bool pos = gv > R(0);
-    for (int d = 0; d < g.dim; ++d) {
-      int a[3] = {i, j, k}, b[3] = {i, j, k};
-      a[d] = map_axis(xyz[d] - 1, g.n[d], g.bc[d][0], g.bc[d][1]);
-      b[d] = map_axis(xyz[d] + 1, g.n[d], g.bc[d][0], g.bc[d][1]);
-      R bw = (x - src[cell_index(g, a[0], a[1], a[2])]) * p.inv_h;
-      R fw = (src[cell_index(g, b[0], b[1], b[2])] - x) * p.inv_h;
-      R t1, t2;
-      if (pos) {
-        t1 = bw > R(0) ? bw * bw : R(0);
-        t2 = fw < R(0) ? fw * fw : R(0);
-      } else {
-        t1 = bw < R(0) ? bw * bw : R(0);
-        t2 = fw > R(0) ? fw * fw : R(0);
-      }
-      G2 += t1 > t2 ? t1 : t2;
-    }
-    R s = pos ? R(1) : R(-1);
-    v = x - dtau * s * (rsqrt_<R>(G2) - R(1));
-  }
-  v = v > p.chimax ? p.chimax : v;
-  v = v < -p.chimax ? -p.chimax : v;
-  dst[c] = v;
-}
 
 template <typename R>
 __global__ void __launch_bounds__(BLOCK) k_init(Grid g, Par<R> p, const R* __restrict__ chi,
@@ -587,14 +501,14 @@ __device__ __forceinline__ void finalize_body(const FinalArgs& f, const double* 
   }
 }
 
-__global__ void __launch_bounds__(FIN_BLOCK) k_finalize(FinalArgs f, const double* __restrict__ part,
+static __global__ void __launch_bounds__(FIN_BLOCK) k_finalize(FinalArgs f, const double* __restrict__ part,
                                                         double* __restrict__ state,
                                                         double* __restrict__ totals) {
   finalize_body(f, part, state, totals);
 }
 
 // one workgroup per instance: part + first[i] NPART holds instance i's records
-__global__ void __launch_bounds__(FIN_BLOCK) k_batch_final(const FinalArgs* __restrict__ fa,
+static __global__ void __launch_bounds__(FIN_BLOCK) k_batch_final(const FinalArgs* __restrict__ fa,
                                                            const int* __restrict__ first,
                                                            const double* __restrict__ part,
                                                            double* __restrict__ states,
@@ -604,12 +518,12 @@ __global__ void __launch_bounds__(FIN_BLOCK) k_batch_final(const FinalArgs* __re
                 totals ? totals + 16ll * i : nullptr);
 }
 
-__global__ void k_reset_state(double* state) {
+static __global__ void k_reset_state(double* state) {
   if (threadIdx.x < NSTATE) state[threadIdx.x] = 0.0;
 }
 
 // the running time from a device value (0 without one)
-__global__ void k_set_time(double* state, const double* t) {
+static __global__ void k_set_time(double* state, const double* t) {
   if (threadIdx.x == 0) state[S_TIME] = t ? *t : 0.0;
 }
 
