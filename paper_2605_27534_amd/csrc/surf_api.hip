@@ -300,16 +300,39 @@ int col_shape(const surf_grid* gr, const surf_params* p, int* strips, int* group
   return *strips * *groups;
 }
 
-// Plane-marching launch shape of the 3D weighted-form transport: strips of
-// COL_OUT columns, blocks of C3_OUT_ROWS rows, chunks of C3_TZ planes (FP32)
-// or C3_TZ64 (FP64).  Returns the workgroup count (0 when the kernel does not
-// apply).
+// Planes per chunk of the 3D weighted-form transport.  A chunk of tz planes
+// marches over tz + 3, so long chunks waste less; but the workgroups run in
+// rounds of two (FP32) or one (FP64) per CU, and a box with few of them leaves
+// the chip idle.  The choice minimizes rounds x (tz + 3): 16 planes at 256^3
+// (1520 workgroups, three rounds), 8 at 128^3 (480 workgroups, one round).
+int col3_planes(const surf_grid* gr, const surf_params* p) {
+  const bool f64 = p->precision == SURF_F64;
+  const long long slots = f64 ? 256 : 512;
+  const long long area = (long long)((gr->n[0] + COL_OUT - 1) / COL_OUT) *
+                         ((gr->n[1] + C3_OUT_ROWS - 1) / C3_OUT_ROWS);
+  int best = 0;
+  long long cost = 0;
+  for (int tz : {32, 24, 16, 12, 8, 4}) {
+    if (tz < 8 && !f64) continue;  // more chunks than reduction records are kept for
+    const long long wgs = area * ((gr->n[2] + tz - 1) / tz);
+    if (tz < (f64 ? 8 : 16) && wgs > 1024) continue;  // the allocation-free step keeps 4096
+    const long long c = (wgs + slots - 1) / slots * (std::min(tz, gr->n[2]) + 3);
+    if (!best || c < cost) {
+      best = tz;
+      cost = c;
+    }
+  }
+  return best;
+}
 
 // the 3D pipelined moving interface keeps a third level-set buffer
 bool snapshot_needed(const surf_grid* gr, const surf_params* p, int nc3) {
   return gr->dim == 3 && nc3 > 0 && p->substep2 == SURF_SUBSTEP2_EXPLICIT &&
          p->interface == SURF_IFACE_VOF;
 }
+// Plane-marching launch shape of the 3D weighted-form transport: strips of
+// COL_OUT columns, blocks of C3_OUT_ROWS rows, chunks of col3_planes planes.
+// Returns the workgroup count (0 when the kernel does not apply).
 int col3_shape(const surf_grid* gr, const surf_params* p, int* s) {
   s[0] = s[1] = s[2] = 0;
   if (gr->dim != 3 || p->flux_form != SURF_FLUX_WEIGHTED) return 0;
@@ -318,9 +341,9 @@ int col3_shape(const surf_grid* gr, const surf_params* p, int* s) {
   // 32-bit byte offsets of the buffer-resource access
   const long long es = p->precision == SURF_F64 ? 8 : 4;
   if ((long long)(gr->n[0] + 1) * (gr->n[1] + 1) * (gr->n[2] + 1) * es > 0x7fffffffll) return 0;
-  const int tz = p->precision == SURF_F64 ? C3_TZ64 : C3_TZ;
   s[0] = (gr->n[0] + COL_OUT - 1) / COL_OUT;
   s[1] = (gr->n[1] + C3_OUT_ROWS - 1) / C3_OUT_ROWS;
+  const int tz = col3_planes(gr, p);
   s[2] = (gr->n[2] + tz - 1) / tz;
   return s[0] * s[1] * s[2];
 }
@@ -761,6 +784,7 @@ void col3d_transport(surf_ctx* c, const void* const* u, const void* F_in, const 
   a.strips = c->c3[0];
   a.yblocks = c->c3[1];
   a.zchunks = c->c3[2];
+  a.tz = col3_planes(&c->grid, &c->prm);
   a.nwg = c->c3_nwg;
   a.per_xcd = (c->c3_nwg + 7) / 8;
   a.Fst = (R*)F_star;

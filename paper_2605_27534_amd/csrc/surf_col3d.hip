@@ -6,9 +6,8 @@ namespace surf {
 
 template <typename R>
 void launch_col3d(hipStream_t st, const Col3Args<R>& a, bool has_u, bool bulk) {
-  constexpr int TZ = sizeof(R) == 4 ? C3_TZ : C3_TZ64;
-  const dim3 grid(8 * a.per_xcd), block(64 * C3_WAVES);
-#define SURF_LAUNCH(...) hipLaunchKernelGGL((k_col3d<R, TZ, __VA_ARGS__>), grid, block, 0, st, a)
+  const dim3 grid(8 * a.per_xcd), block(64 * C3Shape<R>::WAVES);
+#define SURF_LAUNCH(...) hipLaunchKernelGGL((k_col3d<R, __VA_ARGS__>), grid, block, 0, st, a)
   if (a.Pst) {  // the instance that also stores the advected state
     if (has_u && bulk) SURF_LAUNCH(true, true, true);
     else if (has_u) SURF_LAUNCH(true, false, true);

@@ -63,11 +63,18 @@ __device__ __forceinline__ long long face_index(const Grid& g, int d, int i, int
 // reciprocal and square root instructions, ~1 ulp), well inside the FP32
 // parity budget; FP64 keeps the correctly rounded library functions.
 template <typename R> __device__ __forceinline__ R rexp(R x);
-template <> __device__ __forceinline__ float rexp<float>(float x) { return __expf(x); }
+// exp2 and log2 without the library's scaling of denormal results and
+// arguments: e^x below 2^-126 is 0 here (every use adds it to 1 or to a guard),
+// and every logarithm is of a number of at least 1e-6
+template <> __device__ __forceinline__ float rexp<float>(float x) {
+  return __builtin_amdgcn_exp2f(x * 1.44269504088896340736f);
+}
 template <> __device__ __forceinline__ double rexp<double>(double x) { return exp(x); }
 
 template <typename R> __device__ __forceinline__ R rlog(R x);
-template <> __device__ __forceinline__ float rlog<float>(float x) { return __logf(x); }
+template <> __device__ __forceinline__ float rlog<float>(float x) {
+  return __builtin_amdgcn_logf(x) * 0.69314718055994530942f;
+}
 template <> __device__ __forceinline__ double rlog<double>(double x) { return log(x); }
 
 template <typename R> __device__ __forceinline__ R rrcp(R x);
@@ -76,7 +83,7 @@ template <> __device__ __forceinline__ double rrcp<double>(double x) { return 1.
 
 template <typename R> __device__ __forceinline__ R rtanh(R x);
 template <> __device__ __forceinline__ float rtanh<float>(float x) {
-  return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + __expf(2.0f * x));
+  return 1.0f - 2.0f * __builtin_amdgcn_rcpf(1.0f + rexp<float>(2.0f * x));
 }
 template <> __device__ __forceinline__ double rtanh<double>(double x) { return tanh(x); }
 

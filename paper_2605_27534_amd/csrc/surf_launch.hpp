@@ -8,9 +8,8 @@
 
 namespace surf {
 
-// row chunk of k_col2d and plane chunk of k_col3d per precision
+// row chunk of k_col2d per precision
 constexpr int COL_TY = 8, COL_TY64 = 8;
-constexpr int C3_TZ = 16, C3_TZ64 = 8;
 
 // variant: bit 0 the MC limiter, bit 1 the transverse term of substep 1
 template <typename R>
