@@ -1327,20 +1327,25 @@ int iface3_force_impl(surf_ctx* c, const void* vof, const void* sigma, void* con
     a.fc[d] = cap ? (R*)cap[d] : nullptr;
     a.fm[d] = ma ? (R*)ma[d] : nullptr;
   }
+  // the tile list lives in the reduction records, free outside a step: at most
+  // two 4-byte entries per 80-byte record of a 16x8x8 tile (FP64: 8x8x4 tiles)
+  a.list = (int*)c->part;
   const int nx = c->grid.n[0], ny = c->grid.n[1], nz = c->grid.n[2];
-  const int tx = (nx + IF3_T - 1) / IF3_T, ty = (ny + IF3_T - 1) / IF3_T;
-  const long long tiles = (long long)tx * ty * ((nz + IF3_T - 1) / IF3_T);
-  if (tiles >= (1ll << 31)) return SURF_EINVAL;
+  const int rx = (nx + IF3_SX - 1) / IF3_SX, ry = (ny + IF3_T - 1) / IF3_T;
+  const long long regions = (long long)rx * ry * ((nz + IF3_T - 1) / IF3_T);
+  int per[3];
+  long long nfill = 0;
   for (int d = 0; d < 3; ++d) {
     const long long nf = c->ncell / c->grid.n[d] * (c->grid.n[d] + 1);
-    for (R* f : {a.fc[d], a.fm[d]})
-      if (f) hipLaunchKernelGGL(k_zero<R>, dim3((unsigned)((nf + 255) / 256)), dim3(256), 0,
-                                c->stream, f, nf);
+    per[d] = (int)((nf + IF3_FILL - 1) / IF3_FILL);
+    nfill += (long long)per[d] * ((a.fc[d] ? 1 : 0) + (a.fm[d] ? 1 : 0));
   }
-  hipLaunchKernelGGL(k_iface3_cells<R>, dim3((unsigned)tiles), dim3(IF3_NT), 0, c->stream, a,
-                     tx, ty);
-  hipLaunchKernelGGL(k_iface3_faces<R>, dim3((unsigned)tiles), dim3(IF3_NT), 0, c->stream, a,
-                     tx, ty);
+  if (nfill + regions >= (1ll << 31)) return SURF_EINVAL;
+  hipLaunchKernelGGL(k_iface3_begin, dim3(1), dim3(64), 0, c->stream, a.list);
+  hipLaunchKernelGGL(k_iface3_scan<R>, dim3((unsigned)(nfill + regions)), dim3(256), 0, c->stream,
+                     a, per[0], per[1], per[2], (int)nfill, rx, ry);
+  hipLaunchKernelGGL(k_iface3_cells<R>, dim3(IF3_GRID), dim3(128), 0, c->stream, a);
+  hipLaunchKernelGGL(k_iface3_faces<R>, dim3(IF3_GRID), dim3(IF3_FT), 0, c->stream, a);
   if (c->nflags > 0)
     hipLaunchKernelGGL(k_fill_u8, dim3((c->nflags + BLOCK - 1) / BLOCK), dim3(BLOCK), 0,
                        c->stream, c->q[1 - c->chi_cur], (uint8_t)Q_LIVE, c->nflags);

@@ -39,16 +39,30 @@
 // open sides carry no force; on a periodic axis the last face repeats the
 // first.  The geometry runs in FP64 in both precisions.
 //
-// The face arrays are zeroed (k_zero), then two launches over 16^3 tiles (a
-// thread per z-column).  k_iface3_cells lists the tile's interfacial
-// cells in LDS and gives them to its first threads (a sphere's surface
-// leaves a few dozen to a few hundred per tile, so the heavy work packs into
-// a wave or two); it writes each listed cell's height curvature (NaN where
-// no axis closes) and delta_m into two scratch cell arrays, and nothing for
-// the other cells.  k_iface3_faces lists the faces of all three axes with an
-// interfacial cell on either side and computes those, reading the scratch
-// arrays only at interfacial cells and filling in the curvature of a cell
-// without heights from the first array, which no thread writes.
+// Four launches.  k_iface3_begin clears the tile counter.  k_iface3_scan
+// streams: some workgroups zero the face arrays, the others read the fractions
+// and list the 8^3 tiles that hold interfacial cells.  k_iface3_cells takes
+// the listed tiles, two waves each (a sphere's surface leaves some tens of
+// interfacial cells to a tile, one per lane; one wave takes the heights, the
+// other the areas), and writes each interfacial
+// cell's height curvature (NaN where no axis closes) and delta_m into two
+// scratch cell arrays, and nothing for the other cells.  k_iface3_faces takes
+// the listed tiles, lists the faces of their interfacial cells (the low ones,
+// and a high one when the cell beyond is not interfacial, so that no face is
+// computed twice) and computes those, reading the scratch arrays only at
+// interfacial cells and filling in the curvature of a cell without heights
+// from the first array, which no thread writes.
+// At 256^3 FP32 (a sphere of radius 0.3: some 4600 tiles hold 110000
+// interfacial cells) the four take 200 us against 440 for six fills and two
+// passes over all 16^3 tiles, which read the fractions twice and left most
+// lanes of a cut tile's waves idle:
+//   scan 93 us, the zero fill and the one read of the fractions (470 MB: 95 us
+//     at the rate a large copy reaches), so at its bound;
+//   cells 64 us (123 with the fractions read from memory and one wave doing
+//     both parts in turn), bound by the instructions of the 81 LDS reads and
+//     of Newton's method;
+//   faces 38 us (73 with the tile's cells as tasks and branches in every ghost
+//     lookup), bound by the latency of its dependent gathers.
 #pragma once
 #include "surf_capillary.hpp"
 
@@ -67,21 +81,25 @@ struct Iface3Args {
   R* fc[3];  // capillary force per face set (or null)
   R* fm[3];  // Marangoni force per face set (or null)
   double h;
+  int* list;  // [0] the number of listed tiles, then the tiles
 };
 
 __device__ __forceinline__ bool if3_cut(double c) { return c > IFACE_CUT && c < 1.0 - IFACE_CUT; }
 
-// the cell index of (x, y, z) mapped into the box (mirrored or wrapped ghosts)
+// the cell index of (x, y, z) mapped into the box (mirrored or wrapped
+// ghosts); IN: the caller's tile is far enough from every side
+template <bool IN = false>
 __device__ __forceinline__ long long if3_index(const Grid& g, int x, int y, int z) {
-  const int i = map_axis(x, g.n[0], g.bc[0][0], g.bc[0][1]);
-  const int j = map_axis(y, g.n[1], g.bc[1][0], g.bc[1][1]);
-  const int k = map_axis(z, g.n[2], g.bc[2][0], g.bc[2][1]);
+  if constexpr (IN) return cell_index(g, x, y, z);
+  const int i = map_axis_sel(x, g.n[0], g.bc[0][0], g.bc[0][1]);
+  const int j = map_axis_sel(y, g.n[1], g.bc[1][0], g.bc[1][1]);
+  const int k = map_axis_sel(z, g.n[2], g.bc[2][0], g.bc[2][1]);
   return cell_index(g, i, j, k);
 }
 
-template <typename R>
+template <bool IN = false, typename R>
 __device__ __forceinline__ double if3_at(const R* a, const Grid& g, int x, int y, int z) {
-  return (double)a[if3_index(g, x, y, z)];
+  return (double)a[if3_index<IN>(g, x, y, z)];
 }
 
 // ---- PLIC area in the unit cube
@@ -89,58 +107,75 @@ __device__ __forceinline__ double if3_at(const R* a, const Grid& g, int x, int y
 // over [0, t], for 0 <= a <= b: with s = a + b, G is t^2 / (2ab) on [0, a],
 // (t - a/2) / b on [a, b] and symmetric about (s/2, 1/2) (the square's
 // centre), so I(t) = t - s/2 + I(s - t) past s/2.
-__device__ __forceinline__ double plic_G(double a, double b, double t) {
-  const double s = a + b;
-  if (t <= 0.0) return 0.0;
-  if (t >= s) return 1.0;
-  const bool flip = t > 0.5 * s;
-  const double u = flip ? s - t : t;  // in (0, s/2], so u <= b
-  const double g = u <= a ? u * u / (2.0 * a * b) : (u - 0.5 * a) / b;
-  return flip ? 1.0 - g : g;
-}
+// The divisors are taken once (Newton's method evaluates each piece some
+// dozens of times, and an FP64 division is a dozen instructions); 1/(ab) is
+// infinite for a = 0, where its piece is empty.
+struct Plic {
+  double a, b, s, r2ab, r6ab, rb, r2b, ca;
+  __device__ __forceinline__ Plic(double a_, double b_) : a(a_), b(b_), s(a_ + b_) {
+    rb = 1.0 / b;
+    r2b = 0.5 * rb;
+    r2ab = 1.0 / (2.0 * a * b);
+    r6ab = r2ab * (1.0 / 3.0);
+    ca = a * a * rb * (1.0 / 6.0);
+  }
+  __device__ __forceinline__ double G(double t) const {
+    const bool flip = t > 0.5 * s;
+    const double u = flip ? s - t : t;  // up to s/2, so u <= b
+    double g = u <= a ? u * u * r2ab : (u - 0.5 * a) * rb;
+    g = u <= 0.0 ? 0.0 : g;
+    return flip ? 1.0 - g : g;
+  }
+  __device__ __forceinline__ double I(double t) const {
+    const bool flip = t > 0.5 * s;
+    const double u = flip ? s - t : t;
+    double v = u <= a ? u * u * u * r6ab : ca + (u * u - a * u) * r2b;
+    v = u <= 0.0 ? 0.0 : v;
+    return flip ? t - 0.5 * s + v : v;
+  }
+};
 
-__device__ __forceinline__ double plic_I(double a, double b, double t) {
-  const double s = a + b;
-  if (t <= 0.0) return 0.0;
-  if (t >= s) return t - 0.5 * s;
-  const bool flip = t > 0.5 * s;
-  const double u = flip ? s - t : t;
-  const double v =
-      u <= a ? u * u * u / (6.0 * a * b) : a * a / (6.0 * b) + (u * u - a * u) / (2.0 * b);
-  return flip ? t - 0.5 * s + v : v;
-}
-
-__device__ double plic_area3(double m0, double m1, double m2, double c) {
+__device__ __forceinline__ double plic_area3(double m0, double m1, double m2, double c) {
   if (!if3_cut(c)) return 0.0;
-  double n[3] = {fabs(m0), fabs(m1), fabs(m2)};
-  const double s = n[0] + n[1] + n[2];
+  double n0 = fabs(m0), n1 = fabs(m1), n2 = fabs(m2);
+  const double s = n0 + n1 + n2;
   if (!(s > 0.0)) return 0.0;
-  n[0] /= s;
-  n[1] /= s;
-  n[2] /= s;
-  int k = 2;
-  if (n[1] > n[k]) k = 1;
-  if (n[0] > n[k]) k = 0;
-  const double nk = n[k], p = n[k == 0 ? 1 : 0], q = n[k == 2 ? 1 : 2];
-  const double a = fmin(p, q), b = fmax(p, q);
+  const double rs = 1.0 / s;
+  n0 *= rs;
+  n1 *= rs;
+  n2 *= rs;
+  const double nk = fmax(fmax(n0, n1), n2), a = fmin(fmin(n0, n1), n2);
+  const double b = fmax(fmin(n0, n1), fmin(fmax(n0, n1), n2));  // the median
+  const double rk = 1.0 / nk;
+  const Plic q(a, b);
   // the plane leaves the same area cutting off 1 - c from the opposite
   // corner: solve for the smaller volume, where V and G carry no cancellation
   if (c > 0.5) c = 1.0 - c;
-  // V(alpha) = (I(alpha) - I(alpha - nk)) / nk rises from 0 to 1 on [0, 1]
-  double lo = 0.0, hi = 1.0, al = c;
+  // V(alpha) = (I(alpha) - I(alpha - nk)) / nk rises from 0 to 1 on [0, 1]:
+  // alpha^3 / (6 a b nk) up to a, (alpha^2 - a alpha + a^2/3) / (2 b nk) up to b,
+  // (alpha - (a + b)/2) / nk between a + b and nk.  Newton starts from the
+  // inverse of the piece c falls into (the linear one also stands in for the
+  // cubic around b), so that a few steps suffice
+  const double v1 = q.ca * rk, v2 = (b * b - a * b + a * a * (1.0 / 3.0)) * q.r2b * rk;
+  double lo = 0.0, hi = 1.0, al;
+  if (c < v1) al = cbrt(6.0 * a * b * nk * c);
+  else if (c < v2) al = 0.5 * (a + sqrt(fmax(8.0 * b * nk * c - a * a * (1.0 / 3.0), 0.0)));
+  else al = nk * c + 0.5 * (a + b);
+  al = fmin(fmax(al, 1e-300), 1.0);
   for (int it = 0; it < 200; ++it) {
-    const double f = (plic_I(a, b, al) - plic_I(a, b, al - nk)) / nk - c;
+    const double f = (q.I(al) - q.I(al - nk)) * rk - c;
     if (f == 0.0) break;
     if (f < 0.0) lo = al;
     else hi = al;
-    const double dv = (plic_G(a, b, al) - plic_G(a, b, al - nk)) / nk;
+    const double dv = (q.G(al) - q.G(al - nk)) * rk;
     double nx = dv > 0.0 ? al - f / dv : 0.5 * (lo + hi);
     if (!(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);
-    if (nx == al) break;
+    const double step = fabs(nx - al);
     al = nx;
+    if (step <= 1e-15 * al) break;  // rounding: the bracket would only wander
   }
-  const double band = plic_G(a, b, al) - plic_G(a, b, al - nk);
-  return band * sqrt(nk * nk + a * a + b * b) / nk;
+  const double band = q.G(al) - q.G(al - nk);
+  return band * sqrt(nk * nk + a * a + b * b) * rk;
 }
 
 // ---- the cells pass
@@ -173,18 +208,17 @@ __device__ __forceinline__ void if3_youngs(const FV& fv, int x, int y, int z, do
 template <typename FV>
 __device__ __forceinline__ bool if3_heights(const FV& fv, double h, int x, int y, int z,
                                             const double* m, double& kappa) {
-  // axes by |m| descending, ties to the higher axis
-  int ord[3] = {2, 1, 0};
-  for (int u = 0; u < 3; ++u)
-    for (int v = u + 1; v < 3; ++v)
-      if (fabs(m[ord[v]]) > fabs(m[ord[u]])) {
-        const int t = ord[u];
-        ord[u] = ord[v];
-        ord[v] = t;
-      }
+  // axes by |m| descending, ties to the higher axis (scalars, not an indexed
+  // array, which would live in memory)
+  const double f0 = fabs(m[0]), f1 = fabs(m[1]), f2 = fabs(m[2]);
+  const int first = f2 >= f1 && f2 >= f0 ? 2 : (f1 >= f0 ? 1 : 0);
+  const int hi_ = first == 2 ? 1 : 2, lo_ = first == 0 ? 1 : 0;  // the other two
+  const double fh = hi_ == 2 ? f2 : f1, fl = lo_ == 0 ? f0 : f1;
+  const int second = fh >= fl ? hi_ : lo_, third = fh >= fl ? lo_ : hi_;
   for (int q = 0; q < 3; ++q) {
-    const int ax = ord[q];
-    if (m[ax] == 0.0) continue;
+    const int ax = q == 0 ? first : (q == 1 ? second : third);
+    const double ma = ax == 0 ? m[0] : (ax == 1 ? m[1] : m[2]);
+    if (ma == 0.0) continue;
     const int b = ax == 0 ? 1 : 0;
     // the offset along axis e of cell l of column (p, r): l along ax, p along
     // b, r along the third axis (no indexed arrays, so that the 81 loads are
@@ -192,6 +226,7 @@ __device__ __forceinline__ bool if3_heights(const FV& fv, double h, int x, int y
     auto off = [&](int e, int p, int r, int l) { return e == ax ? l : (e == b ? p : r); };
     double H[9];
     bool ok = true;
+#pragma unroll
     for (int pr = 0; pr < 9; ++pr) {  // column (p, r) = (pr / 3 - 1, pr % 3 - 1)
       const int p = pr / 3 - 1, r = pr % 3 - 1;
       double col[2 * IF3_HL + 1];  // the column's nine values gathered together
@@ -202,7 +237,7 @@ __device__ __forceinline__ bool if3_heights(const FV& fv, double h, int x, int y
 #pragma unroll
       for (int l = 0; l <= 2 * IF3_HL; ++l) sum += col[l];
       const double lo = col[0], hi = col[2 * IF3_HL];
-      const double full = m[ax] > 0.0 ? lo : hi, empty = m[ax] > 0.0 ? hi : lo;
+      const double full = ma > 0.0 ? lo : hi, empty = ma > 0.0 ? hi : lo;
       if (!(full >= 1.0 - IFACE_CUT && empty <= IFACE_CUT)) ok = false;
       H[pr] = sum;
     }
@@ -220,34 +255,84 @@ __device__ __forceinline__ bool if3_heights(const FV& fv, double h, int x, int y
   return false;
 }
 
-constexpr int IF3_T = 16, IF3_NT = IF3_T * IF3_T;  // 16^3 tiles, a thread per z-column
-constexpr int IF3_S = IF3_T + 2 * IF3_HL;           // the staged region's edge
+constexpr int IF3_T = 8;                   // 8^3 tiles
+constexpr int IF3_S = IF3_T + 2 * IF3_HL;  // the staged region's edge
+constexpr int IF3_SX = 64;                 // cells along x per scanning workgroup (8 tiles)
+constexpr int IF3_FILL = 1 << 14;          // values zeroed per filling workgroup
+constexpr int IF3_GRID = 1024;             // persistent workgroups over the listed tiles
 
-// The workgroup's list of this thread's entries (the set bits k of mask,
-// stored as (k << 8) | t | tag, tag above bit 11) after those of the
-// threads before it, in sList; returns the list length.  Two barriers.
-__device__ __forceinline__ int if3_list(unsigned mask, unsigned short* sList, int* sWave,
-                                        unsigned tag = 0) {
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int cnt = __popc(mask);
-  int inc = cnt;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int up = __shfl_up(inc, o);
-    if (lane >= o) inc += up;
+__global__ void k_iface3_begin(int* list) {
+  if (threadIdx.x == 0) list[0] = 0;
+}
+
+// The first nfill workgroups zero the face arrays, fill_wgs[d] workgroups for
+// each array of the face set d; the others scan 64 x 8 x 8 cells each and
+// append their tiles that hold interfacial cells to the list.
+template <typename R>
+__global__ void __launch_bounds__(256) k_iface3_scan(Iface3Args<R> a, int fill0, int fill1,
+                                                     int fill2, int nfill, int regions_x,
+                                                     int regions_y) {
+  const Grid& g = a.g;
+  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+  const int t = threadIdx.x;
+  int b = blockIdx.x;
+  if (b < nfill) {
+    const int per[3] = {fill0, fill1, fill2};
+    for (int set = 0; set < 2; ++set)
+      for (int d = 0; d < 3; ++d) {
+        R* f = set ? a.fm[d] : a.fc[d];
+        if (!f) continue;
+        if (b >= per[d]) {
+          b -= per[d];
+          continue;
+        }
+        const long long n = (long long)(nx + (d == 0)) * (ny + (d == 1)) * (nz + (d == 2));
+        const long long lo = (long long)b * IF3_FILL, hi = lo + IF3_FILL < n ? lo + IF3_FILL : n;
+        constexpr int V = 16 / (int)sizeof(R);
+        if ((((size_t)f) & 15) == 0) {
+          const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+          for (long long q = lo + (long long)t * V; q + V <= hi; q += 256 * V) *(float4*)(f + q) = z;
+          const long long tail = lo + (hi - lo) / V * V;
+          if (tail + t < hi) f[tail + t] = R(0);
+        } else {
+          for (long long q = lo + t; q < hi; q += 256) f[q] = R(0);
+        }
+        return;
+      }
+    return;
   }
-  if (lane == 63) sWave[w] = inc;
-  __syncthreads();
-  int pos = inc - cnt, total = 0;
+  b -= nfill;
+  __shared__ unsigned sBits[4];
+  const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int rx = b % regions_x, r = b / regions_x, ry = r % regions_y, rz = r / regions_y;
+  const int x = rx * IF3_SX + lane, y0 = ry * IF3_T + 2 * wv, z0 = rz * IF3_T;
+  const int xc = x < nx ? x : nx - 1;
+  R v[16];
 #pragma unroll
-  for (int v = 0; v < IF3_NT / 64; ++v) {
-    pos += v < w ? sWave[v] : 0;
-    total += sWave[v];
+  for (int k = 0; k < 16; ++k) {
+    const int y = min(y0 + (k & 1), ny - 1), z = min(z0 + (k >> 1), nz - 1);
+    v[k] = a.vof[(long long)xc + (long long)nx * (y + (long long)ny * z)];
   }
-  for (unsigned m = mask; m; m &= m - 1u)
-    sList[pos++] = (unsigned short)((((__ffs(m) - 1) << 8) | t) | tag);
+  // cells past the box repeat its last row or plane, which belongs to the same
+  // tile or to one listed anyway; lanes past it vote for nothing
+  bool cut = false;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) cut = cut || if3_cut((double)v[k]);
+  const unsigned long long m = __ballot(cut && x < nx);
+  unsigned bits = 0;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) bits |= ((m >> (8 * q)) & 0xffull) ? (1u << q) : 0u;
+  if (lane == 0) sBits[wv] = bits;
   __syncthreads();
-  return total;
+  if (t == 0) {
+    unsigned all = sBits[0] | sBits[1] | sBits[2] | sBits[3];
+    if (all) {
+      int at = 1 + atomicAdd(a.list, __popc(all));
+      const int tx = (nx + IF3_T - 1) / IF3_T, ty = (ny + IF3_T - 1) / IF3_T;
+      for (; all; all &= all - 1u)
+        a.list[at++] = rx * (IF3_SX / IF3_T) + __ffs(all) - 1 + tx * (ry + ty * rz);
+    }
+  }
 }
 
 // the face index of cell (x, y, z) with coordinate d replaced by f
@@ -257,71 +342,81 @@ __device__ __forceinline__ long long if3_face_index(const Grid& g, int d, int x,
 }
 
 template <typename R>
-__global__ void __launch_bounds__(IF3_NT) k_iface3_cells(Iface3Args<R> a, int tiles_x,
-                                                        int tiles_y) {
+__global__ void __launch_bounds__(128) k_iface3_cells(Iface3Args<R> a) {
   __shared__ unsigned short sList[IF3_T * IF3_T * IF3_T];
-  __shared__ int sWave[IF3_NT / 64];
   __shared__ float sV[IF3_S][IF3_S][IF3_S];  // FP32 fractions of the tile and its halo
   const Grid& g = a.g;
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-  const int t = threadIdx.x;
-  const int r = blockIdx.x / tiles_x;
-  const int x0 = (blockIdx.x % tiles_x) * IF3_T, y0 = (r % tiles_y) * IF3_T,
-            z0 = (r / tiles_y) * IF3_T;
-  const int x = x0 + t % IF3_T, y = y0 + t / IF3_T;
-  const long long pl = (long long)nx * ny;
-  // this column's interfacial cells as a bit mask, every load issued first
-  unsigned mask = 0;
-  if (x < nx && y < ny) {
-    const long long cxy = (long long)x + (long long)nx * y;
-    R v[IF3_T];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tx = (nx + IF3_T - 1) / IF3_T, ty = (ny + IF3_T - 1) / IF3_T;
+  const int count = a.list[0];
+  for (int i = blockIdx.x; i < count; i += gridDim.x) {
+    const int tile = a.list[1 + i];
+    const int x0 = (tile % tx) * IF3_T, y0 = (tile / tx % ty) * IF3_T, z0 = tile / (tx * ty) * IF3_T;
+    const int x = x0 + (lane & 7), y = y0 + (lane >> 3);
+    if constexpr (sizeof(R) == 4) {
+      // FP32: the tile and IF3_HL cells around it (mapped) staged in LDS
+      __syncthreads();  // the last tile's reads are done
 #pragma unroll
-    for (int k = 0; k < IF3_T; ++k) v[k] = z0 + k < nz ? a.vof[cxy + pl * (z0 + k)] : R(0);
+      for (int h = 0; h < IF3_S * IF3_S / 128; ++h) {  // a z-column of the region each
+        const int q = (int)threadIdx.x + 128 * h, sx = q % IF3_S, sy = q / IF3_S;
+        R v[IF3_S];
 #pragma unroll
-    for (int k = 0; k < IF3_T; ++k) mask |= if3_cut((double)v[k]) ? (1u << k) : 0u;
-  }
-  const int total = if3_list(mask, sList, sWave);
-  if (total == 0) return;
-  auto cell = [&](const auto& fv) {
-    for (int i = t; i < total; i += IF3_NT) {
-      const int e = sList[i];
-      const int cx = x0 + (e & 15), cy = y0 + ((e >> 4) & 15), cz = z0 + (e >> 8);
-      const long long cl = (long long)cx + (long long)nx * cy + pl * cz;
-      const double c = (double)a.vof[cl];
-      double m3[3], kap = 0.0;
-      if3_youngs(fv, cx, cy, cz, m3);
-      if (!if3_heights(fv, a.h, cx, cy, cz, m3, kap)) kap = (double)NAN;
-      a.kh[cl] = (R)kap;
-      a.dm[cl] = (R)(plic_area3(m3[0], m3[1], m3[2], c) / a.h);
-    }
-  };
-  if constexpr (sizeof(R) == 4) {
-    // FP32: the tile and IF3_HL cells around it (mapped) staged in LDS, a
-    // column of 24 per thread with its loads issued together
-    for (int q = t; q < IF3_S * IF3_S; q += IF3_NT) {
-      const int sx = q % IF3_S, sy = q / IF3_S;
-      R v[IF3_S];
+        for (int k = 0; k < IF3_S; ++k)
+          v[k] = a.vof[if3_index(g, x0 - IF3_HL + sx, y0 - IF3_HL + sy, z0 - IF3_HL + k)];
 #pragma unroll
-      for (int k = 0; k < IF3_S; ++k)
-        v[k] = a.vof[if3_index(g, x0 - IF3_HL + sx, y0 - IF3_HL + sy, z0 - IF3_HL + k)];
-#pragma unroll
-      for (int k = 0; k < IF3_S; ++k) sV[k][sy][sx] = v[k];
+        for (int k = 0; k < IF3_S; ++k) sV[k][sy][sx] = v[k];
+      }
     }
     __syncthreads();
-    cell([&](int X, int Y, int Z) {
-      return (double)sV[Z - z0 + IF3_HL][Y - y0 + IF3_HL][X - x0 + IF3_HL];
-    });
-  } else {
-    cell([&](int X, int Y, int Z) { return if3_at(a.vof, g, X, Y, Z); });
+    // the tile's interfacial cells in the order of planes and lanes (both waves
+    // write the same list)
+    int total = 0;
+#pragma unroll
+    for (int k = 0; k < IF3_T; ++k) {
+      const bool in = x < nx && y < ny && z0 + k < nz;
+      double c = 0.0;
+      if constexpr (sizeof(R) == 4)
+        c = (double)sV[k + IF3_HL][(lane >> 3) + IF3_HL][(lane & 7) + IF3_HL];
+      else if (in)
+        c = (double)a.vof[cell_index(g, x, y, z0 + k)];
+      const bool cut = in && if3_cut(c);
+      const unsigned long long m = __ballot(cut);
+      if (cut) sList[total + __popcll(m & ((1ull << lane) - 1ull))] = (unsigned short)((k << 6) | lane);
+      total += __popcll(m);
+    }
+    __syncthreads();
+    auto cell = [&](const auto& fv) {
+      for (int q = lane; q < total; q += 64) {
+        const int e = sList[q];
+        const int cx = x0 + (e & 7), cy = y0 + ((e >> 3) & 7), cz = z0 + (e >> 6);
+        const long long cl = cell_index(g, cx, cy, cz);
+        const double c = (double)fv(cx, cy, cz);
+        double m3[3], kap = 0.0;
+        if3_youngs(fv, cx, cy, cz, m3);
+        if (wv == 0) {  // uniform
+          if (!if3_heights(fv, a.h, cx, cy, cz, m3, kap)) kap = (double)NAN;
+          a.kh[cl] = (R)kap;
+        } else {
+          a.dm[cl] = (R)(plic_area3(m3[0], m3[1], m3[2], c) / a.h);
+        }
+      }
+    };
+    if constexpr (sizeof(R) == 4)
+      cell([&](int X, int Y, int Z) {
+        return (double)sV[Z - z0 + IF3_HL][Y - y0 + IF3_HL][X - x0 + IF3_HL];
+      });
+    else
+      cell([&](int X, int Y, int Z) { return if3_at(a.vof, g, X, Y, Z); });
   }
 }
 
 // ---- the faces pass
 // the level set's curvature at cell (x, y, z), moved to the interface
-template <typename R>
+template <bool IN, typename R>
 __device__ __forceinline__ double if3_levelset_kappa(const Iface3Args<R>& a, int x, int y, int z) {
   const double h = a.h;
-  auto C = [&](int dx, int dy, int dz) { return if3_at(a.chi, a.g, x + dx, y + dy, z + dz); };
+  auto C = [&](int dx, int dy, int dz) { return if3_at<IN>(a.chi, a.g, x + dx, y + dy, z + dz); };
   const double c0 = C(0, 0, 0);
   const double gx = (C(1, 0, 0) - C(-1, 0, 0)) / (2.0 * h);
   const double gy = (C(0, 1, 0) - C(0, -1, 0)) / (2.0 * h);
@@ -341,7 +436,7 @@ __device__ __forceinline__ double if3_levelset_kappa(const Iface3Args<R>& a, int
 }
 
 // kappa of an interfacial cell (mapped coordinates)
-template <typename R>
+template <bool IN, typename R>
 __device__ __forceinline__ double if3_kappa(const Iface3Args<R>& a, int x, int y, int z) {
   const double kh = (double)a.kh[cell_index(a.g, x, y, z)];
   if (!isnan(kh)) return kh;
@@ -350,7 +445,7 @@ __device__ __forceinline__ double if3_kappa(const Iface3Args<R>& a, int x, int y
   R fv[27], kv[27];
 #pragma unroll
   for (int q = 0; q < 27; ++q) {
-    const long long i = if3_index(a.g, x + q % 3 - 1, y + (q / 3) % 3 - 1, z + q / 9 - 1);
+    const long long i = if3_index<IN>(a.g, x + q % 3 - 1, y + (q / 3) % 3 - 1, z + q / 9 - 1);
     fv[q] = a.vof[i];
     kv[q] = a.kh[i];
   }
@@ -365,16 +460,17 @@ __device__ __forceinline__ double if3_kappa(const Iface3Args<R>& a, int x, int y
       ++cnt;
     }
   }
-  return cnt ? s / cnt : if3_levelset_kappa(a, x, y, z);
+  return cnt ? s / cnt : if3_levelset_kappa<IN>(a, x, y, z);
 }
 
 // the face gradient of a cell field across the face between cells L and R
 // (R = L + e_d, both mapped into the box)
-template <typename R>
-__device__ __forceinline__ void if3_face_grad(const Iface3Args<R>& a, const R* f, int d, const int* L,
-                              const int* Rc, double* gr) {
-  const double h = a.h;
-  const double nrm = (if3_at(f, a.g, Rc[0], Rc[1], Rc[2]) - if3_at(f, a.g, L[0], L[1], L[2])) / h;
+template <bool IN, typename R>
+__device__ __forceinline__ void if3_face_grad(const Iface3Args<R>& a, const R* f, int d,
+                                              const int* L, const int* Rc, double* gr) {
+  const double ih = 1.0 / a.h, iq = 0.25 * ih;
+  const double nrm =
+      (if3_at<IN>(f, a.g, Rc[0], Rc[1], Rc[2]) - if3_at<IN>(f, a.g, L[0], L[1], L[2])) * ih;
 #pragma unroll
   for (int t = 0; t < 3; ++t) {
     double s = 0.0;
@@ -383,157 +479,118 @@ __device__ __forceinline__ void if3_face_grad(const Iface3Args<R>& a, const R* f
       const int* X = side == 0 ? L : Rc;
       const int px = X[0] + (t == 0), py = X[1] + (t == 1), pz = X[2] + (t == 2);
       const int qx = X[0] - (t == 0), qy = X[1] - (t == 1), qz = X[2] - (t == 2);
-      s += 0.5 * (if3_at(f, a.g, px, py, pz) - if3_at(f, a.g, qx, qy, qz)) / (2.0 * h);
+      s += (if3_at<IN>(f, a.g, px, py, pz) - if3_at<IN>(f, a.g, qx, qy, qz)) * iq;
     }
     gr[t] = t == d ? nrm : s;
   }
 }
 
 // the two forces on the face along d between cells L and R
-template <typename R>
-__device__ __forceinline__ void if3_face(const Iface3Args<R>& a, int d, const int* L, const int* Rc, double& cap,
-                         double& ma) {
+template <bool IN, typename R>
+__device__ __forceinline__ void if3_face(const Iface3Args<R>& a, int d, const int* L,
+                                         const int* Rc, double& cap, double& ma) {
   const long long iL = cell_index(a.g, L[0], L[1], L[2]), iR = cell_index(a.g, Rc[0], Rc[1], Rc[2]);
   const double cL = (double)a.vof[iL], cR = (double)a.vof[iR];
   const bool cutL = if3_cut(cL), cutR = if3_cut(cR);
   cap = ma = 0.0;
-  // kappa and delta_m vanish on both sides: so do both forces
-  if (!cutL && !cutR) return;
-  const double kL = cutL ? if3_kappa(a, L[0], L[1], L[2]) : 0.0;
-  const double kR = cutR ? if3_kappa(a, Rc[0], Rc[1], Rc[2]) : 0.0;
+  // every load that needs no decision comes first, the gradients' among them
+  double gs[3], gc[3];
+  if3_face_grad<IN>(a, a.sig, d, L, Rc, gs);
+  if3_face_grad<IN>(a, a.chi, d, L, Rc, gc);
+  const double dL = (double)a.dm[iL], dR = (double)a.dm[iR];
+  const double kL = cutL ? if3_kappa<IN>(a, L[0], L[1], L[2]) : 0.0;
+  const double kR = cutR ? if3_kappa<IN>(a, Rc[0], Rc[1], Rc[2]) : 0.0;
   const double kf = cutL && cutR ? 0.5 * (kL + kR) : (cutL ? kL : (cutR ? kR : 0.0));
   const double sf = 0.5 * ((double)a.sig[iL] + (double)a.sig[iR]);
   cap = -sf * kf * (cR - cL) / a.h;
-  double gs[3], gc[3];
-  if3_face_grad(a, a.sig, d, L, Rc, gs);
-  if3_face_grad(a, a.chi, d, L, Rc, gc);
-  const double nrm = fmax(sqrt(gc[0] * gc[0] + gc[1] * gc[1] + gc[2] * gc[2]), 1e-6);
-  const double n0 = gc[0] / nrm, n1 = gc[1] / nrm, n2 = gc[2] / nrm;
+  const double rn = 1.0 / fmax(sqrt(gc[0] * gc[0] + gc[1] * gc[1] + gc[2] * gc[2]), 1e-6);
+  const double n0 = gc[0] * rn, n1 = gc[1] * rn, n2 = gc[2] * rn;
   const double nd = d == 0 ? n0 : (d == 1 ? n1 : n2);
   const double ndot = n0 * gs[0] + n1 * gs[1] + n2 * gs[2];
-  const double dmf = 0.5 * ((cutL ? (double)a.dm[iL] : 0.0) + (cutR ? (double)a.dm[iR] : 0.0));
+  const double dmf = 0.5 * ((cutL ? dL : 0.0) + (cutR ? dR : 0.0));
   const double gsd = d == 0 ? gs[0] : (d == 1 ? gs[1] : gs[2]);
   ma = dmf * (gsd - nd * ndot);
 }
 
-// The faces next to interfacial cells, over 16^3 tiles: the low face of a
-// cell along d is computed when the cell or its low neighbour along d is
-// interfacial (on a periodic axis the last cell also its high face, the
-// same two cells as face 0), the other faces keep the zero the cells pass
-// wrote.  Per axis the tile lists its faces in LDS and its threads take them
-// in turn, so the interfacial work of a tile packs into a wave or two.
+// The faces of the listed tiles' interfacial cells: the low face of each along
+// every axis, and its high face when the cell beyond is not interfacial (that
+// cell's low face otherwise); on a periodic axis face n is face 0, written by
+// whoever computes face 0.  Faces on other sides keep the zero.
+constexpr int IF3_FT = 256;  // threads
 template <typename R>
-__global__ void __launch_bounds__(IF3_NT) k_iface3_faces(Iface3Args<R> a, int tiles_x,
-                                                        int tiles_y) {
-  __shared__ unsigned short sList[3 * (IF3_T * IF3_T * IF3_T + IF3_NT)];
-  __shared__ int sWave[IF3_NT / 64];
+__global__ void __launch_bounds__(IF3_FT) k_iface3_faces(Iface3Args<R> a) {
+  __shared__ unsigned short sList[6 * IF3_T * IF3_T * IF3_T];
+  __shared__ int sCount;
   const Grid& g = a.g;
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const int t = threadIdx.x;
-  const int r = blockIdx.x / tiles_x;
-  const int x0 = (blockIdx.x % tiles_x) * IF3_T, y0 = (r % tiles_y) * IF3_T,
-            z0 = (r / tiles_y) * IF3_T;
-  const int x = x0 + t % IF3_T, y = y0 + t / IF3_T;
-  const bool colin = x < nx && y < ny;
-  const long long pl = (long long)nx * ny;
-  // cut bits of the column (bit k: cell z0 + k) and of the column's low
-  // neighbours along x and y, the cell below the column and, for the last
-  // cells along an axis, the first cell along it
-  unsigned cc = 0, cxm = 0, cym = 0;
-  bool czm = false, cz0 = false;
-  if (colin) {
-    const long long cxy = (long long)x + (long long)nx * y;
-    const long long xm = (long long)(x == 0 ? nx - 1 : x - 1) + (long long)nx * y;
-    const long long ym = (long long)x + (long long)nx * (y == 0 ? ny - 1 : y - 1);
-    R v[IF3_T], vx[IF3_T], vy[IF3_T];
+  const int tx = (nx + IF3_T - 1) / IF3_T, ty = (ny + IF3_T - 1) / IF3_T;
+  const int count = a.list[0];
+  for (int i = blockIdx.x; i < count; i += gridDim.x) {
+    const int tile = a.list[1 + i];
+    const int x0 = (tile % tx) * IF3_T, y0 = (tile / tx % ty) * IF3_T, z0 = tile / (tx * ty) * IF3_T;
+    // a tile's faces read up to two cells beyond it: where those lie in the box
+    // no ghost lookup is needed (faces 64 -> 38 us at 256^3, most of it address
+    // arithmetic)
+    const bool in = x0 >= 2 && y0 >= 2 && z0 >= 2 && x0 + IF3_T + 2 <= nx &&
+                    y0 + IF3_T + 2 <= ny && z0 + IF3_T + 2 <= nz;
+    __syncthreads();  // the last tile's list is done with
+    if (t == 0) sCount = 0;
+    __syncthreads();
+    constexpr int CPT = IF3_T * IF3_T * IF3_T / IF3_FT;  // cells per thread
+    R v[CPT];
 #pragma unroll
-    for (int k = 0; k < IF3_T; ++k) {
-      const long long z = (long long)min(z0 + k, nz - 1);
-      v[k] = a.vof[cxy + pl * z];
-      vx[k] = a.vof[xm + pl * z];
-      vy[k] = a.vof[ym + pl * z];
+    for (int k = 0; k < CPT; ++k) {
+      const int c = t + IF3_FT * k;
+      const int x = x0 + (c & 7), y = y0 + ((c >> 3) & 7), z = z0 + (c >> 6);
+      v[k] = x < nx && y < ny && z < nz ? a.vof[cell_index(g, x, y, z)] : R(0);
     }
-    const R vz = a.vof[cxy + pl * (z0 == 0 ? nz - 1 : z0 - 1)];  // the cell below
-    const R vz0 = a.vof[cxy];                                     // z = 0
 #pragma unroll
-    for (int k = 0; k < IF3_T; ++k) {
-      const unsigned b = z0 + k < nz ? (1u << k) : 0u;
-      cc |= if3_cut((double)v[k]) ? b : 0u;
-      cxm |= if3_cut((double)vx[k]) ? b : 0u;
-      cym |= if3_cut((double)vy[k]) ? b : 0u;
-    }
-    czm = if3_cut((double)vz);
-    cz0 = if3_cut((double)vz0);
-  }
-  // per axis the low faces (bit k when the face exists, interior or
-  // periodic, and a side is interfacial) and the high faces of the last
-  // cells on a periodic axis (the cell or the first one along the axis)
-  int n = 0;
-  for (int d = 0; d < 3; ++d) {
-    const bool per = g.bc[d][0] == BC_PERIODIC;
-    unsigned lo = 0, hi = 0;
-    if (colin) {
-      if (d == 0) {
-        lo = (x > 0 || per) ? (cc | cxm) : 0u;
-      } else if (d == 1) {
-        lo = (y > 0 || per) ? (cc | cym) : 0u;
-      } else {
-        const unsigned below = (cc << 1) | (czm ? 1u : 0u);  // bit k: cell z0 + k - 1
-        lo = (cc | below) & ((1u << IF3_T) - 1u);
-        if (z0 == 0 && !per) lo &= ~1u;
-      }
-      if (per) {
-        if (d == 0 && x == nx - 1) {
-          unsigned first = 0;  // the row's first cells
-          for (int k = 0; k < IF3_T; ++k)
-            if (z0 + k < nz && if3_cut((double)a.vof[(long long)nx * y + pl * (z0 + k)]))
-              first |= 1u << k;
-          hi = cc | first;
-        } else if (d == 1 && y == ny - 1) {
-          unsigned first = 0;  // the column's first cells
-          for (int k = 0; k < IF3_T; ++k)
-            if (z0 + k < nz && if3_cut((double)a.vof[(long long)x + pl * (z0 + k)])) first |= 1u << k;
-          hi = cc | first;
-        } else if (d == 2 && nz - 1 >= z0 && nz - 1 < z0 + IF3_T) {
-          const int k = nz - 1 - z0;
-          if (((cc >> k) & 1u) || cz0) hi = 1u << k;
+    for (int k = 0; k < CPT; ++k) {
+      if (!if3_cut((double)v[k])) continue;
+      const int c = t + IF3_FT * k;
+      const int X[3] = {x0 + (c & 7), y0 + ((c >> 3) & 7), z0 + (c >> 6)};
+      unsigned tasks = 0;  // bit d: low face, bit 3 + d: high face
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        const bool per = g.bc[d][0] == BC_PERIODIC;
+        if (X[d] > 0 || per) tasks |= 1u << d;
+        if (X[d] < g.n[d] - 1 || per) {
+          const int q = X[d] == g.n[d] - 1 ? 0 : X[d] + 1;
+          const R nb = a.vof[cell_index(g, d == 0 ? q : X[0], d == 1 ? q : X[1], d == 2 ? q : X[2])];
+          if (!if3_cut((double)nb)) tasks |= 8u << d;
         }
       }
-      const unsigned inbox = z0 + IF3_T <= nz ? 0xffffu : ((1u << (nz - z0)) - 1u);
-      lo &= inbox;
-      hi &= inbox;
+      int at = atomicAdd(&sCount, __popc(tasks));
+      for (; tasks; tasks &= tasks - 1u)
+        sList[at++] = (unsigned short)(((__ffs(tasks) - 1) << 9) | c);
     }
-    // tag: the axis in bits 12-13, a high face in bit 14
-    n += if3_list(lo, sList + n, sWave, (unsigned)d << 12);
-    n += if3_list(hi, sList + n, sWave, ((unsigned)d << 12) | (1u << 14));
+    __syncthreads();
+    const int n = sCount;
+    for (int q = t; q < n; q += IF3_FT) {
+      const int e = sList[q], c = e & 511, k = e >> 9, d = k % 3;
+      const int X[3] = {x0 + (c & 7), y0 + ((c >> 3) & 7), z0 + (c >> 6)};
+      const int nd = g.n[d], xd = d == 0 ? X[0] : (d == 1 ? X[1] : X[2]);
+      int f = xd + (k >= 3 ? 1 : 0);
+      if (f == nd) f = 0;  // periodic
+      const int ld = f == 0 ? nd - 1 : f - 1;
+      const int Rc[3] = {d == 0 ? f : X[0], d == 1 ? f : X[1], d == 2 ? f : X[2]};
+      const int L[3] = {d == 0 ? ld : X[0], d == 1 ? ld : X[1], d == 2 ? ld : X[2]};
+      double fc = 0.0, fm = 0.0;
+      if (in) if3_face<true>(a, d, L, Rc, fc, fm);
+      else if3_face<false>(a, d, L, Rc, fc, fm);
+      R* cap = d == 0 ? a.fc[0] : (d == 1 ? a.fc[1] : a.fc[2]);
+      R* ma = d == 0 ? a.fm[0] : (d == 1 ? a.fm[1] : a.fm[2]);
+      const long long fi = if3_face_index(g, d, X[0], X[1], X[2], f);
+      if (cap) cap[fi] = (R)fc;
+      if (ma) ma[fi] = (R)fm;
+      if (f == 0) {  // only a periodic axis has tasks on face 0
+        const long long fn = if3_face_index(g, d, X[0], X[1], X[2], nd);
+        if (cap) cap[fn] = (R)fc;
+        if (ma) ma[fn] = (R)fm;
+      }
+    }
   }
-  for (int i = t; i < n; i += IF3_NT) {
-    const int e = sList[i];
-    const int d = (e >> 12) & 3;
-    const bool high = (e >> 14) & 1;
-    const int cx = x0 + (e & 15), cy = y0 + ((e >> 4) & 15), cz = z0 + ((e >> 8) & 15);
-    const int X[3] = {cx, cy, cz};
-    const int nd = g.n[d], xd = d == 0 ? cx : (d == 1 ? cy : cz);
-    const int f = high ? nd : xd;  // face coordinate along d
-    const int rd = f == nd ? 0 : f, ld = f == 0 ? nd - 1 : f - 1;
-    const int Rc[3] = {d == 0 ? rd : X[0], d == 1 ? rd : X[1], d == 2 ? rd : X[2]};
-    const int L[3] = {d == 0 ? ld : X[0], d == 1 ? ld : X[1], d == 2 ? ld : X[2]};
-    double fc = 0.0, fm = 0.0;
-    if3_face(a, d, L, Rc, fc, fm);
-    const long long fi = if3_face_index(g, d, cx, cy, cz, f);
-    R* cap = d == 0 ? a.fc[0] : (d == 1 ? a.fc[1] : a.fc[2]);
-    R* ma = d == 0 ? a.fm[0] : (d == 1 ? a.fm[1] : a.fm[2]);
-    if (cap) cap[fi] = (R)fc;
-    if (ma) ma[fi] = (R)fm;
-  }
-}
-
-// zero over n values (the face arrays, before the interfacial faces are
-// written)
-template <typename R>
-__global__ void __launch_bounds__(256) k_zero(R* __restrict__ p, long long n) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) p[i] = R(0);
 }
 
 }  // namespace surf

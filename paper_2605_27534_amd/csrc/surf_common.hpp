@@ -49,6 +49,15 @@ __device__ __forceinline__ int map_axis(int q, int n, int lo_bc, int hi_bc) {
   return q;
 }
 
+// map_axis written with selects only (no branches)
+__device__ __forceinline__ int map_axis_sel(int q, int n, int lo_bc, int hi_bc) {
+  const int lo = lo_bc == BC_PERIODIC ? q + n : -1 - q;
+  const int hi = hi_bc == BC_PERIODIC ? q - n : 2 * n - 1 - q;
+  int r = q < 0 ? lo : (q >= n ? hi : q);
+  r = r < 0 ? 0 : r;
+  return r >= n ? n - 1 : r;
+}
+
 __device__ __forceinline__ long long cell_index(const Grid& g, int i, int j, int k) {
   return (long long)i + (long long)g.n[0] * ((long long)j + (long long)g.n[1] * k);
 }

@@ -41,16 +41,6 @@ struct Geo3Args {
   int per_xcd;  // ceil(ntiles / 8): tiles per XCD band of the classify grid
 };
 
-// map_axis written with selects only (no branches), for the uniform z
-// coordinates and the per-thread x, y neighbours
-__device__ __forceinline__ int map_axis_sel(int q, int n, int lo_bc, int hi_bc) {
-  const int lo = lo_bc == BC_PERIODIC ? q + n : -1 - q;
-  const int hi = hi_bc == BC_PERIODIC ? q - n : 2 * n - 1 - q;
-  int r = q < 0 ? lo : (q >= n ? hi : q);
-  r = r < 0 ? 0 : r;
-  return r >= n ? n - 1 : r;
-}
-
 __device__ __forceinline__ int geo3_tile_of(const Geo3Args& t, int x, int y, int z) {
   return (x / G3) + t.tiles[0] * ((y / G3) + t.tiles[1] * (z / G3));
 }
