@@ -709,7 +709,10 @@ void geo3_impl(surf_ctx* c, const void* vof, hipStream_t st = nullptr, bool thir
     Timed tm(c, 1, st);
     R* chiT = third ? (R*)c->chi_snap : nullptr;
     uint8_t* qT = third ? c->q_snap : nullptr;
-    hipLaunchKernelGGL(k_geo3_classify<R>, dim3(8 * ga.per_xcd), dim3(G3_THREADS), 0, st,
+    // lane offsets within a plane: 32 bits reach 4 GiB
+    const bool wide = (unsigned long long)c->grid.n[0] * c->grid.n[1] * sizeof(R) > 0xffffffffull;
+    auto classify = wide ? k_geo3_classify<R, unsigned long long> : k_geo3_classify<R, unsigned>;
+    hipLaunchKernelGGL(classify, dim3(8 * ga.per_xcd), dim3(G3_THREADS), 0, st,
                        ga, p, (const R*)vof, chiS, (R*)c->g0, (const uint8_t*)qR, qS, chiT, qT,
                        c->state);
     hipLaunchKernelGGL(k_geo3_list, dim3(1), dim3(G3_LIST_THREADS), 0, st,
@@ -719,12 +722,15 @@ void geo3_impl(surf_ctx* c, const void* vof, hipStream_t st = nullptr, bool thir
     // sweeps S -> R (S -> T)
     R* chiE = third ? chiT : chiR;
     uint8_t* qE = third ? qT : qR;
+    const int grid = std::min((c->ng3 + 7) / 8 * 8, G3_SWEEP_GRID);
     for (int k = 1; k <= K; ++k) {
       const R* src = (k & 1) ? (k == 1 ? chiR : chiE) : chiS;
       R* dst = (k & 1) ? chiS : chiE;
-      hipLaunchKernelGGL(k_geo3_sweep<R>, dim3(G3_SWEEP_GRID), dim3(G3_SWEEP_THREADS), 0,
-                         st, ga, p, dtau, src, dst, (const R*)c->g0, qE,
-                         (const int*)c->live3, k == K ? 1 : 0);
+      auto sweep = wide ? (k == K ? k_geo3_sweep<R, unsigned long long, true>
+                                  : k_geo3_sweep<R, unsigned long long, false>)
+                        : (k == K ? k_geo3_sweep<R, unsigned, true> : k_geo3_sweep<R, unsigned, false>);
+      hipLaunchKernelGGL(sweep, dim3(grid), dim3(G3_SWEEP_THREADS), 0, st, ga, p, dtau, src, dst,
+                         (const R*)c->g0, (const uint8_t*)qS, qE, (const int*)c->live3);
     }
   }
   c->materialized = true;
