@@ -25,7 +25,9 @@
 // unbounded; bounded below by 1/2, it is at most zeta eps |grad phi|, and
 // every profile up to twice the equilibrium width keeps the unit normal.
 // Each face flux is evaluated by both of its cells with the same arithmetic
-// in the same order, so the update conserves sum(phi) exactly.  s is taken of
+// in the same order, so the update conserves sum(phi) exactly (in 3D without
+// the substep-1 variants both substeps run in the marching form of
+// surf_acdi3d.hpp).  s is taken of
 // phi clamped into [0, 1]; re-initialization from a VoF field (k_acdi_init)
 // sets phi = 1/(1 + e^{chi/eps}) from the level set.  On axisymmetric rings
 // (Appendix B) the fluxes are the same expressions in (r, z), and a radial
@@ -131,10 +133,11 @@ __global__ void __launch_bounds__(BLOCK) k_acdi_init(Grid g, Par<R> p, const R* 
   phi[c] = ph;
 }
 
-// substep 1 for phi, and s of the result.  Every load (the 5-cell stencil
+// substep 1 for phi, and s of the result (3D with the minmod limiter and no
+// transverse term: k_acdi3_adv).  Every load (the 5-cell stencil
 // along each axis, both face velocities) is issued up front from indices
 // mapped into the grid; the boundary cases only select among the results.
-template <typename R, int DIM, bool VAR = false>
+template <typename R, int DIM, bool VAR>
 __global__ void __launch_bounds__(ACDI_TX) k_acdi_adv(AcdiArgs<R> a, const R* __restrict__ phi,
                                                       const R* __restrict__ u0,
                                                       const R* __restrict__ u1,
@@ -190,12 +193,12 @@ __global__ void __launch_bounds__(ACDI_TX) k_acdi_adv(AcdiArgs<R> a, const R* __
   s[c] = acdi_s<R>(st, a.p.eps, a.ve);
 }
 
-// The regularization substep, then the level set of the new phi.  s on the
-// 3^DIM block around the cell and phi* on the cell and its face neighbours
-// are loaded up front (indices mapped into the grid); each face flux is then
-// formed from registers.  A face's flux is computed by both of its cells from
-// the same values in the same order.
-template <typename R, int DIM>
+// The regularization substep of a 2D grid, then the level set of the new phi
+// (3D: k_acdi3_reg).  s on the 3x3 block around the cell and phi* on the cell
+// and its face neighbours are loaded up front (indices mapped into the grid);
+// each face flux is then formed from registers.  A face's flux is computed by
+// both of its cells from the same values in the same order.
+template <typename R>
 __global__ void __launch_bounds__(ACDI_TX) k_acdi_reg(AcdiArgs<R> a, const R* __restrict__ phs,
                                                       const R* __restrict__ s,
                                                       R* __restrict__ phi_out,
@@ -205,64 +208,42 @@ __global__ void __launch_bounds__(ACDI_TX) k_acdi_reg(AcdiArgs<R> a, const R* __
   int x[3];
   long long c;
   if (!acdi_cell(g, x, c)) return;
-  constexpr int NZ = DIM == 3 ? 3 : 1;
-  int m[3][3];  // m[d][k]: the cell coordinate x[d] + k - 1, mapped
+  int m[2][3];  // m[d][k]: the cell coordinate x[d] + k - 1, mapped
 #pragma unroll
-  for (int d = 0; d < 3; ++d)
+  for (int d = 0; d < 2; ++d)
 #pragma unroll
-    for (int k = 0; k < 3; ++k)
-      m[d][k] = d < DIM ? map_axis(x[d] + k - 1, g.n[d], g.bc[d][0], g.bc[d][1]) : x[d];
-  R S[NZ][3][3];
+    for (int k = 0; k < 3; ++k) m[d][k] = map_axis(x[d] + k - 1, g.n[d], g.bc[d][0], g.bc[d][1]);
+  R S[3][3];  // S[ky][kx]
 #pragma unroll
-  for (int kz = 0; kz < NZ; ++kz)
+  for (int ky = 0; ky < 3; ++ky)
 #pragma unroll
-    for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-      for (int kx = 0; kx < 3; ++kx)
-        S[kz][ky][kx] = s[cell_index(g, m[0][kx], m[1][ky], DIM == 3 ? m[2][kz] : x[2])];
-  R P[DIM][3];  // phi* at offsets -1, 0, +1 along each axis
+    for (int kx = 0; kx < 3; ++kx) S[ky][kx] = s[cell_index(g, m[0][kx], m[1][ky], x[2])];
+  R P[2][3];  // phi* at offsets -1, 0, +1 along each axis
   const R pc = phs[c];
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) {
-    int lo[3] = {x[0], x[1], x[2]}, hi[3] = {x[0], x[1], x[2]};
-    lo[d] = m[d][0];
-    hi[d] = m[d][2];
-    P[d][0] = phs[cell_index(g, lo[0], lo[1], lo[2])];
+  for (int d = 0; d < 2; ++d) {
+    P[d][0] = phs[cell_index(g, d ? x[0] : m[0][0], d ? m[1][0] : x[1], x[2])];
     P[d][1] = pc;
-    P[d][2] = phs[cell_index(g, hi[0], hi[1], hi[2])];
+    P[d][2] = phs[cell_index(g, d ? x[0] : m[0][2], d ? m[1][2] : x[1], x[2])];
   }
-  // s at the block offsets (k0, k1, k2) along axes 0, 1, 2 (each 0..2)
-  auto sat = [&](int k0, int k1, int k2) { return S[DIM == 3 ? k2 : 0][k1][k0]; };
   R wlo, whi;
   acdi_ring_weights(a, x[0], wlo, whi);
   R acc = R(0);
 #pragma unroll
-  for (int d = 0; d < DIM; ++d) {
+  for (int d = 0; d < 2; ++d) {
     const bool per = g.bc[d][0] == BC_PERIODIC;
+    // s at offset k along d and j along the other axis (each 0..2)
+    auto sat = [&](int k, int j) { return d == 0 ? S[j][k] : S[k][j]; };
     R G[2];
 #pragma unroll
     for (int sd = 0; sd < 2; ++sd) {
       const int kL = sd, kR = sd + 1;  // the face's cells along d
-      int oL[3] = {1, 1, 1}, oR[3] = {1, 1, 1};
-      oL[d] = kL;
-      oR[d] = kR;
-      const R sL = sat(oL[0], oL[1], oL[2]), sR = sat(oR[0], oR[1], oR[2]);
+      const R sL = sat(kL, 1), sR = sat(kR, 1);
       const R gn = (sR - sL) * p.inv_h;
-      R g2 = gn * gn;
-#pragma unroll
-      for (int t = 0; t < DIM; ++t) {
-        if (t == d) continue;
-        int lp[3] = {oL[0], oL[1], oL[2]}, lm[3] = {oL[0], oL[1], oL[2]};
-        int rp[3] = {oR[0], oR[1], oR[2]}, rm[3] = {oR[0], oR[1], oR[2]};
-        lp[t] = 2;
-        lm[t] = 0;
-        rp[t] = 2;
-        rm[t] = 0;
-        const R cdL = (sat(lp[0], lp[1], lp[2]) - sat(lm[0], lm[1], lm[2])) * (R(0.5) * p.inv_h);
-        const R cdR = (sat(rp[0], rp[1], rp[2]) - sat(rm[0], rm[1], rm[2])) * (R(0.5) * p.inv_h);
-        const R gt = R(0.5) * (cdL + cdR);
-        g2 += gt * gt;
-      }
+      const R cdL = (sat(kL, 2) - sat(kL, 0)) * (R(0.5) * p.inv_h);
+      const R cdR = (sat(kR, 2) - sat(kR, 0)) * (R(0.5) * p.inv_h);
+      const R gt = R(0.5) * (cdL + cdR);
+      const R g2 = gn * gn + gt * gt;
       const R nd = rdiv<R>(gn, fmax(rsqrt_<R>(g2), R(0.5)));
       const R T = rtanh<R>(R(0.5) * (sL + sR) * (R(0.5) * p.inv_eps));
       const R f = a.zeta * (p.eps * (P[d][kR] - P[d][kL]) * p.inv_h - R(0.25) * (R(1) - T * T) * nd);

@@ -68,6 +68,20 @@ __device__ __forceinline__ long long face_index(const Grid& g, int d, int i, int
   return (long long)i + mx * ((long long)j + my * k);
 }
 
+// Access at a scalar base and a lane's byte offset of type O (32 bits where the
+// span is below 4 GiB).  The empty statement keeps the offset's widening
+// beside its use, where it costs nothing.
+template <typename R, typename O>
+__device__ __forceinline__ R lane_ld(const R* base, O off) {
+  asm("" : "+v"(off));
+  return *(const R*)((const char*)base + off);
+}
+template <typename R, typename O>
+__device__ __forceinline__ void lane_st(R v, R* base, O off) {
+  asm("" : "+v"(off));
+  *(R*)((char*)base + off) = v;
+}
+
 // Elementary functions.  FP32 uses the hardware approximations (exp2, log2,
 // reciprocal and square root instructions, ~1 ulp), well inside the FP32
 // parity budget; FP64 keeps the correctly rounded library functions.

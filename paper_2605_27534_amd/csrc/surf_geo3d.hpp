@@ -47,18 +47,6 @@ struct Geo3Args {
   int per_xcd;  // ceil(ntiles / 8): tiles per XCD band of the classify grid
 };
 
-// access at a scalar base and a lane's byte offset of type O
-template <typename R, typename O>
-__device__ __forceinline__ R geo3_ld(const R* base, O off) {
-  asm("" : "+v"(off));
-  return *(const R*)((const char*)base + off);
-}
-template <typename R, typename O>
-__device__ __forceinline__ void geo3_st(R v, R* base, O off) {
-  asm("" : "+v"(off));
-  *(R*)((char*)base + off) = v;
-}
-
 // ---- access within 16-lane rows: lanes 16 r .. 16 r + 15 hold one row of a
 // tile.  edge holds, in the row's first and last lane, the value beyond that
 // end of the row.
@@ -122,7 +110,7 @@ __global__ void __launch_bounds__(G3_THREADS) k_geo3_classify(Geo3Args ga, Par<R
   bool one = true, zero = true;
   R f[G3];
 #pragma unroll
-  for (int k = 0; k < G3; ++k) f[k] = geo3_ld<R, O>(plane(k), co);
+  for (int k = 0; k < G3; ++k) f[k] = lane_ld<R, O>(plane(k), co);
 #pragma unroll
   for (int k = 0; k < G3; ++k) {
     const bool out = !colin | (z0 + k >= nz);
@@ -188,8 +176,8 @@ __global__ void __launch_bounds__(G3_THREADS) k_geo3_classify(Geo3Args ga, Par<R
   const O eo = (row + (O)ex) * (O)sizeof(R);
   const O mo = ((O)nx * (O)map_axis_sel(gy - 1, ny, g.bc[1][0], g.bc[1][1]) + (O)cx) * (O)sizeof(R);
   const O po = ((O)nx * (O)map_axis_sel(gy + 1, ny, g.bc[1][0], g.bc[1][1]) + (O)cx) * (O)sizeof(R);
-  R zlo = geo3_ld<R, O>(vof + pl * map_axis(z0 - 1, nz, g.bc[2][0], g.bc[2][1]), co);
-  R zhi = geo3_ld<R, O>(vof + pl * map_axis(z0 + G3, nz, g.bc[2][0], g.bc[2][1]), co);
+  R zlo = lane_ld<R, O>(vof + pl * map_axis(z0 - 1, nz, g.bc[2][0], g.bc[2][1]), co);
+  R zhi = lane_ld<R, O>(vof + pl * map_axis(z0 + G3, nz, g.bc[2][0], g.bc[2][1]), co);
   auto x_of = [&](R v) { return (v - R(0.5)) * p.h; };
   zlo = x_of(zlo);
   zhi = x_of(zhi);
@@ -203,9 +191,9 @@ __global__ void __launch_bounds__(G3_THREADS) k_geo3_classify(Geo3Args ga, Par<R
 #pragma unroll
     for (int j = 0; j < G3 / 2; ++j) {
       const R* const pz = plane(half * (G3 / 2) + j);
-      ne[j] = geo3_ld<R, O>(pz, eo);
-      nym[j] = geo3_ld<R, O>(pz, mo);
-      nyp[j] = geo3_ld<R, O>(pz, po);
+      ne[j] = lane_ld<R, O>(pz, eo);
+      nym[j] = lane_ld<R, O>(pz, mo);
+      nyp[j] = lane_ld<R, O>(pz, po);
     }
 #pragma unroll
     for (int j = 0; j < G3 / 2; ++j) {
@@ -241,7 +229,7 @@ __global__ void __launch_bounds__(G3_THREADS) k_geo3_classify(Geo3Args ga, Par<R
   R* const gz0 = g0 + pl * z0;
 #pragma unroll
   for (int k = 0; k < G3; ++k)
-    if (colin & (z0 + k < nz)) geo3_st<R, O>(pin[k], gz0 + pl * k, co);
+    if (colin & (z0 + k < nz)) lane_st<R, O>(pin[k], gz0 + pl * k, co);
 }
 
 // live[0] = count, live[1 + r] = the r-th live tile in tile order
@@ -346,10 +334,10 @@ __global__ void __launch_bounds__(G3_SWEEP_THREADS) k_geo3_sweep(Geo3Args ga, Pa
         const bool own = k >= 0 && k < G3_SZ;
 #pragma unroll
         for (int r = own ? -1 : 0; r < G3_ROWS + (own ? 1 : 0); ++r) {
-          c[k + 1][r + 1] = geo3_ld<R, O>(sp, ro[r + 1]);
+          c[k + 1][r + 1] = lane_ld<R, O>(sp, ro[r + 1]);
           if (own && r >= 0 && r < G3_ROWS) {
-            e[k][r] = geo3_ld<R, O>(sp, eo[r]);
-            gv[k][r] = code == G3_CUT ? geo3_ld<R, O>(gp, ro[r + 1]) : side;
+            e[k][r] = lane_ld<R, O>(sp, eo[r]);
+            gv[k][r] = code == G3_CUT ? lane_ld<R, O>(gp, ro[r + 1]) : side;
           }
         }
       }
@@ -368,7 +356,7 @@ __global__ void __launch_bounds__(G3_SWEEP_THREADS) k_geo3_sweep(Geo3Args ga, Pa
                        hj_axis<R>(w, fold(c[k][r + 1]), fold(c[k + 2][r + 1]));
           const R nv = fold(hj_finish<R>(p, dtau, w, fabs(s), G2));
           if (gx < nx && gy + r < ny) {
-            geo3_st<R, O>(nv, dp, ro[r + 1]);
+            lane_st<R, O>(nv, dp, ro[r + 1]);
             if (LAST) {
               allpos = allpos && nv == p.chimax;
               allneg = allneg && nv == -p.chimax;
