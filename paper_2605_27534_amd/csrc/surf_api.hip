@@ -1430,12 +1430,15 @@ Par<R> par_of(const surf_grid& gr, const surf_params& q) {
 template <typename R, int DIM, bool BULK>
 void adj_launch(hipStream_t st, const AdjArgs<R>& a, dim3 grid, dim3 block, int which) {
   if (which == 0) hipLaunchKernelGGL((k_adv_star<R, DIM, BULK>), grid, block, 0, st, a);
-  else if (which == 1) hipLaunchKernelGGL((k_adj_src<R, DIM, BULK>), grid, block, 0, st, a);
-  else {
-    // interior x tiles plus one workgroup of side columns per row block
-    const dim3 gs(adj_xtiles(a.g.n[0]) + 1, grid.y, grid.z);
-    if (a.has_u) hipLaunchKernelGGL((k_adj_adv<R, DIM, BULK, true>), gs, block, 0, st, a);
-    else hipLaunchKernelGGL((k_adj_adv<R, DIM, BULK, false>), gs, block, 0, st, a);
+  else if (which == 1) {
+    if constexpr (DIM == 2) hipLaunchKernelGGL((k_adj_src<R, BULK>), grid, block, 0, st, a);
+  } else {
+    // lane offsets within a plane: 32 bits reach 4 GiB
+    using W = unsigned long long;
+    const bool wide = (W)(a.g.n[0] + 1) * (a.g.n[1] + 1) * sizeof(R) > 0xffffffffull;
+    auto k = a.has_u ? (wide ? k_adj_adv<R, W, DIM, BULK, true> : k_adj_adv<R, unsigned, DIM, BULK, true>)
+                     : k_adj_adv<R, unsigned, DIM, BULK, false>;
+    hipLaunchKernelGGL(k, grid, block, 0, st, a);
   }
 }
 
@@ -1449,6 +1452,30 @@ void adj_launch(hipStream_t st, const AdjArgs<R>& a, int dim, bool bulk, dim3 gr
     if (bulk) adj_launch<R, 3, true>(st, a, grid, block, which);
     else adj_launch<R, 3, false>(st, a, grid, block, which);
   }
+}
+
+// Substep 2 and the source in 3D; returns the number of dL/dtheta records.
+// Planes per chunk: 8, or fewer where that leaves the chip without two waves
+// per SIMD (a chunk forms two planes beyond its own).
+template <typename R>
+int adj3_source(hipStream_t st, const AdjArgs<R>& a, bool bulk) {
+  Adj3Args<R> q;
+  q.a = a;
+  const int *n = a.g.n, rows = Adj3Shape<R>::N * ADJ3_WAVES;
+  q.strips = (n[0] + ADJ3_X - 1) / ADJ3_X;
+  q.ygroups = (n[1] + rows - 1) / rows;
+  q.tz = 8;
+  while (q.tz > 1 && (long long)q.strips * q.ygroups * ADJ3_WAVES * ((n[2] + q.tz - 1) / q.tz) < 2048)
+    q.tz /= 2;
+  q.nwg = q.strips * q.ygroups * ((n[2] + q.tz - 1) / q.tz);
+  q.per_xcd = (q.nwg + 7) / 8;
+  // lane offsets within a plane: 32 bits reach 4 GiB
+  using W = unsigned long long;
+  const bool wide = (W)n[0] * n[1] * sizeof(R) > 0xffffffffull;
+  auto k = bulk ? (wide ? k_adj3_src<R, W, true> : k_adj3_src<R, unsigned, true>)
+                : (wide ? k_adj3_src<R, W, false> : k_adj3_src<R, unsigned, false>);
+  hipLaunchKernelGGL(k, dim3(8 * q.per_xcd), dim3(64 * ADJ3_WAVES), 0, st, q);
+  return q.nwg;
 }
 
 template <typename R>
@@ -1483,7 +1510,7 @@ int adjoint_step_impl(surf_ctx* c, const void* const* u, const void* F, const vo
   const dim3 agrid((c->grid.n[0] + ADJ_TX - 1) / ADJ_TX, (c->grid.n[1] + ADJ_TY - 1) / ADJ_TY,
                    c->grid.n[2]);
   const dim3 ablock(ADJ_TX * ADJ_TY);
-  const int nb = (int)(agrid.x * agrid.y * agrid.z);
+  int nb = (int)(agrid.x * agrid.y * agrid.z);
   if (given) {
     // xi* from the caller
   } else if (a.has_u) {
@@ -1496,7 +1523,8 @@ int adjoint_step_impl(surf_ctx* c, const void* const* u, const void* F, const vo
     if (hipMemcpyAsync(c->adj[1], psi, bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
       return SURF_EDEVICE;
   }
-  adj_launch<R>(c->stream, a, c->grid.dim, c->prm.bulk_enabled != 0, agrid, ablock, 1);
+  if (c->grid.dim == 3) nb = adj3_source<R>(c->stream, a, c->prm.bulk_enabled != 0);
+  else adj_launch<R>(c->stream, a, 2, c->prm.bulk_enabled != 0, agrid, ablock, 1);
   adj_launch<R>(c->stream, a, c->grid.dim, c->prm.bulk_enabled != 0, agrid, ablock, 2);
   hipLaunchKernelGGL(k_adj_final, dim3(1), dim3(FIN_BLOCK), 0, c->stream,
                      (const double*)c->adj_part, nb, dtheta);
