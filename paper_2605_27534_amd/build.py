@@ -3,7 +3,8 @@
     python -m paper_2605_27534_amd.build
 
 The kernel families with many instances are translation units of their own,
-compiled once per precision; all units compile in parallel.
+compiled once per precision (the 2D transport also once per number of rows a
+wave takes); all units compile in parallel.
 """
 from __future__ import annotations
 
@@ -17,8 +18,12 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsurf.so")
-PER_PRECISION = ["surf_col2d.hip", "surf_batch_col2d.hip", "surf_col3d.hip", "surf_hj.hip"]
-UNITS = [("surf_api.hip", None)] + [(f, r) for r in ("float", "double") for f in PER_PRECISION]
+PER_PRECISION = ["surf_batch_col2d.hip", "surf_col3d.hip", "surf_hj.hip"]
+# (source, macros), the longest to compile first
+UNITS = ([("surf_col2d.hip", ("SURF_REAL=" + r, "SURF_ROWS=%d" % n))
+          for n in (8, 4, 2) for r in ("double", "float")]
+         + [("surf_api.hip", ())]
+         + [(f, ("SURF_REAL=" + r,)) for r in ("double", "float") for f in PER_PRECISION])
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -30,11 +35,9 @@ FLAGS = [
 
 
 def _compile(unit, out, verbose):
-    src, real = unit
-    obj = os.path.join(out, "%s_%s.o" % (src[:-4], real))
-    cmd = [HIPCC, *FLAGS, "-c", "-o", obj, os.path.join(CSRC, src)]
-    if real:
-        cmd.insert(-3, "-DSURF_REAL=" + real)
+    src, macros = unit
+    obj = os.path.join(out, "_".join([src[:-4], *(m.split("=")[1] for m in macros)]) + ".o")
+    cmd = [HIPCC, *FLAGS, *("-D" + m for m in macros), "-c", "-o", obj, os.path.join(CSRC, src)]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)

@@ -66,7 +66,7 @@ struct surf_ctx {
 
   int per_xcd;
   // 2D weighted-form transport: column-streaming waves
-  int col_strips, col_groups, col_nwg;
+  int col_strips, col_groups, col_nwg, col_rows;
   // 3D weighted-form transport: plane-marching workgroups (strips, row
   // blocks, plane chunks)
   int c3[3], c3_nwg;
@@ -285,18 +285,31 @@ int ntiles_2d(const surf_grid* gr, int* t) {
 }
 
 // Column-streaming launch shape of the 2D weighted-form transport: strips of
-// COL_OUT columns, row chunks of COL_TY rows (FP32) or COL_TY64 (FP64),
-// COL_WAVES chunks per workgroup.  Returns the workgroup count (0 when the
-// kernel does not apply).
-int col_shape(const surf_grid* gr, const surf_params* p, int* strips, int* groups) {
+// COL_OUT columns, chunks of `rows` rows, COL_WAVES chunks per workgroup.
+// Returns the workgroup count (0 when the kernel does not apply).
+// Rows per wave: a wave marches down its rows one after another and computes
+// two more than it owns, so few rows are for boxes that leave the chip idle.
+// 2 while that gives every SIMD at most two waves, 4 while it gives at most
+// four (FP32) or six (FP64), else 8.  With 2, 4, 8 rows the kernel takes (us,
+// with flow)
+//   FP32  128^2  6.2  7.6 10.7   512^2  8.1  8.5 10.9   733 x 611  9.7  8.9 11.1
+//         1024^2 17.3 15.0 15.2  1500 x 1300 27.6 22.9 22.0
+//   FP64  128^2  7.9 10.2 16.3   512^2 13.9 13.5 16.8   733 x 611 16.2 14.2 19.5
+//         1024^2 32.9 28.4 32.5  1500 x 1300 56.4 46.7 44.2
+// and beside the geometry of the next step, where the rows computed twice cost
+// the other kernel its share, 16 steps at 1024^2 (FP32) take 506 us with 4
+// rows and 477 with 8.
+int col_shape(const surf_grid* gr, const surf_params* p, int* strips, int* groups, int* rows) {
   *strips = *groups = 0;
+  *rows = 8;
   if (gr->dim != 2 || p->flux_form != SURF_FLUX_WEIGHTED) return 0;
   // 32-bit byte offsets of the buffer-resource access
   const long long es = p->precision == SURF_F64 ? 8 : 4;
   if ((long long)(gr->n[0] + 1) * (gr->n[1] + 1) * es > 0x7fffffffll) return 0;
-  int ty = p->precision == SURF_F64 ? COL_TY64 : COL_TY;
-  int chunks = (gr->n[1] + ty - 1) / ty;
   *strips = (gr->n[0] + COL_OUT - 1) / COL_OUT;
+  auto waves = [&](int r) { return (long long)*strips * ((gr->n[1] + r - 1) / r); };
+  *rows = waves(2) <= 2 * 1024 ? 2 : (waves(4) <= (es == 4 ? 4 : 6) * 1024 ? 4 : 8);
+  const int chunks = (gr->n[1] + *rows - 1) / *rows;
   *groups = (chunks + COL_WAVES - 1) / COL_WAVES;
   return *strips * *groups;
 }
@@ -800,7 +813,9 @@ void col2d_transport(surf_ctx* c, const void* const* u, const void* F_in, const 
   a.nwg = c->col_nwg;
   a.per_xcd = (c->col_nwg + 7) / 8;
   const int variant = (c->prm.limiter ? 1 : 0) + (c->prm.transverse ? 2 : 0);
-  launch_col2d<R>(c->stream, c->grid.axisym != 0, variant, a, has_u, bulk);
+  auto launch = c->col_rows == 2 ? launch_col2d<R, 2>
+                                 : (c->col_rows == 4 ? launch_col2d<R, 4> : launch_col2d<R, 8>);
+  launch(c->stream, c->grid.axisym != 0, variant, a, has_u, bulk);
 }
 
 // The 3D weighted-form transport kernel alone, on the context's stream.
@@ -1556,8 +1571,8 @@ int surf_workspace_bytes(const surf_grid* grid, const surf_params* params, size_
   int tiles[3], t2[2];
   int nblk = nblocks_step(grid, params, tiles);
   int n2 = ntiles_2d(grid, t2);
-  int cs, cg;
-  int ncol = col_shape(grid, params, &cs, &cg);
+  int cs, cg, cr;
+  int ncol = col_shape(grid, params, &cs, &cg, &cr);
   // the weighted form on rings runs on k_col2d only (the paper form in k_step2d)
   if (grid->axisym && ncol == 0 && params->flux_form == SURF_FLUX_WEIGHTED) return SURF_EINVAL;
   // so do the explicit substep-1 variants in 2D (3D: the tile transport)
@@ -1632,7 +1647,7 @@ int surf_init(surf_ctx** out, const surf_grid* grid, const surf_params* params, 
   c->ngtiles = geo_tiles(grid, params, c->gtiles);
   c->ng3 = geo3_tiles(grid, c->g3tiles);
   c->nflags = flag_count(grid, params);
-  c->col_nwg = col_shape(grid, params, &c->col_strips, &c->col_groups);
+  c->col_nwg = col_shape(grid, params, &c->col_strips, &c->col_groups, &c->col_rows);
   c->c3_nwg = col3_shape(grid, params, c->c3);
   int npart = c->nblk > c->ntiles2d ? c->nblk : c->ntiles2d;
   npart = c->col_nwg > npart ? c->col_nwg : npart;
@@ -2899,6 +2914,16 @@ int static_scratch(double** out) {
   return SURF_OK;
 }
 
+// The workgroup count that bounds the grids of the allocation-free step (see
+// the header): chunks of 8 rows in 2D, of 16 (FP32) or 8 planes in 3D, whatever
+// chunks the launch itself takes.
+long long static_workgroups(const surf_grid& g, int precision) {
+  const long long strips = (g.n[0] + COL_OUT - 1) / COL_OUT;
+  if (g.dim == 2) return strips * (((g.n[1] + 7) / 8 + COL_WAVES - 1) / COL_WAVES);
+  const int tz = precision == SURF_F64 ? 8 : 16;
+  return strips * ((g.n[1] + C3_OUT_ROWS - 1) / C3_OUT_ROWS) * ((g.n[2] + tz - 1) / tz);
+}
+
 // The running state of one call: time and cumulative outflow from the
 // caller's totals (zero without them), status and flags cleared.
 __global__ void k_static_state(double* __restrict__ state, const double* __restrict__ totals) {
@@ -2943,11 +2968,12 @@ int surf_step_static(const surf_grid* grid, const surf_params* params, double dt
   }
   c.stream = (hipStream_t)hip_stream;
   c.ncell = (long long)grid->n[0] * grid->n[1] * grid->n[2];
-  c.col_nwg = col_shape(grid, params, &c.col_strips, &c.col_groups);
+  c.col_nwg = col_shape(grid, params, &c.col_strips, &c.col_groups, &c.col_rows);
   c.c3_nwg = col3_shape(grid, params, c.c3);
   const int nwg = grid->dim == 2 ? c.col_nwg : c.c3_nwg;
   if (nwg == 0) return SURF_EINVAL;  // beyond the 32-bit offsets of the transport kernels
-  if (nwg > STATIC_MAX_WG) return SURF_ENOMEM;
+  if (nwg > STATIC_MAX_WG || static_workgroups(*grid, params->precision) > STATIC_MAX_WG)
+    return SURF_ENOMEM;
   double* base = nullptr;
   rc = static_scratch(&base);
   if (rc) return rc;

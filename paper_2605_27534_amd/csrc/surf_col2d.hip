@@ -1,13 +1,12 @@
 // surf_col2d.hip -- launcher of the 2D column-streaming transport, compiled
-// once per precision (SURF_REAL).
+// once per precision (SURF_REAL) and number of rows per wave (SURF_ROWS).
 #include "surf_launch.hpp"
 
 namespace surf {
 
-template <typename R>
+template <typename R, int TY>
 void launch_col2d(hipStream_t st, bool axisym, int variant, const ColArgs<R>& a, bool has_u,
                   bool bulk) {
-  constexpr int TY = sizeof(R) == 4 ? COL_TY : COL_TY64;
   const dim3 grid(8 * a.per_xcd), block(64 * COL_WAVES);
 #define SURF_LAUNCH(...) hipLaunchKernelGGL((k_col2d<R, TY, __VA_ARGS__>), grid, block, 0, st, a)
   if (axisym) {
@@ -49,7 +48,7 @@ void launch_col2d(hipStream_t st, bool axisym, int variant, const ColArgs<R>& a,
 #undef SURF_LAUNCH
 }
 
-template void launch_col2d<SURF_REAL>(hipStream_t, bool, int, const ColArgs<SURF_REAL>&, bool,
-                                      bool);
+template void launch_col2d<SURF_REAL, SURF_ROWS>(hipStream_t, bool, int, const ColArgs<SURF_REAL>&,
+                                                 bool, bool);
 
 }  // namespace surf

@@ -8,11 +8,9 @@
 
 namespace surf {
 
-// row chunk of k_col2d per precision
-constexpr int COL_TY = 8, COL_TY64 = 8;
-
-// variant: bit 0 the MC limiter, bit 1 the transverse term of substep 1
-template <typename R>
+// k_col2d with TY rows per wave (2, 4 or 8); variant: bit 0 the MC limiter,
+// bit 1 the transverse term of substep 1
+template <typename R, int TY>
 void launch_col2d(hipStream_t st, bool axisym, int variant, const ColArgs<R>& a, bool has_u,
                   bool bulk);
 template <typename R>
