@@ -23,10 +23,13 @@ void launch_hj2(hipStream_t st, bool many, const HjArgs<R>& a) {
 template <typename R>
 void launch_hj3(hipStream_t st, bool many, bool first, const HjArgs<R>& a) {
   const dim3 grid(8 * a.per_xcd), block(256);
-  if (many && first) hipLaunchKernelGGL((k_hj3<R, 2, true>), grid, block, 0, st, a);
-  else if (many) hipLaunchKernelGGL((k_hj3<R, 2, false>), grid, block, 0, st, a);
-  else if (first) hipLaunchKernelGGL((k_hj3<R, 1, true>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_hj3<R, 1, false>), grid, block, 0, st, a);
+  constexpr bool F32 = sizeof(R) == 4;
+  const bool off32 = F32 && (unsigned long long)a.g.n[0] * a.g.n[1] * sizeof(R) <= 0xffffffffull;
+  auto k = many ? (first ? (off32 ? k_hj3<R, 2, true, F32> : k_hj3<R, 2, true, false>)
+                         : (off32 ? k_hj3<R, 2, false, F32> : k_hj3<R, 2, false, false>))
+                : (first ? (off32 ? k_hj3<R, 1, true, F32> : k_hj3<R, 1, true, false>)
+                         : (off32 ? k_hj3<R, 1, false, F32> : k_hj3<R, 1, false, false>));
+  hipLaunchKernelGGL(k, grid, block, 0, st, a);
 }
 
 template void launch_pin<SURF_REAL>(hipStream_t, dim3, const Grid&, const Par<SURF_REAL>&,

@@ -208,7 +208,7 @@ __global__ void __launch_bounds__(256) k_hj2(HjArgs<R> a) {
 // fewer waves), of 6 planes 1.12 ms; consecutive blocks on different XCDs,
 // instead of slabs of one XCD, 1.37 against 1.21 ms.
 constexpr int HJ3_X = 60, HJ3_Y = 4, HJ3_Z = 4, HJ3_HALO = 2;
-template <typename R, int S, bool FIRST>
+template <typename R, int S, bool FIRST, bool OFF32>
 __global__ void __launch_bounds__(256) k_hj3(HjArgs<R> a) {
   constexpr int NR = HJ3_Y + 2 * S, NZ = HJ3_Z + 2 * S, LA = sizeof(R) == 4 ? 4 : 2, ES = (int)sizeof(R);
   // XCD x (workgroups b with b % 8 == x) takes the z blocks x, x + 8, ...:
@@ -258,9 +258,8 @@ __global__ void __launch_bounds__(256) k_hj3(HjArgs<R> a) {
   }
   const int mx = map_axis(xs, nx, g.bc[0][0], g.bc[0][1]);
   const int vmx = mx * ES, vxs = xs * ES;
-  // a plane has under 2^30 cells: FP32 rows take 32-bit byte offsets from the
-  // plane, FP64 ones a pointer each
-  constexpr bool OFF32 = ES == 4;
+  // OFF32 (FP32, planes of at most 4 GiB): rows take 32-bit byte offsets from the
+  // plane; else a pointer each
   unsigned ro[NR], vo[NR];
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
