@@ -479,7 +479,8 @@ def main():
         ab = ACDI_WORDS_PER_CELL * es
         out["config"]["acdi_reinit_every"] = reinit
         out["acdi"] = {
-            "kernels": "k_acdi_adv + k_acdi_reg", "avg_step_us": round(acdi_ms * 1e3, 3),
+            "kernels": ("k_acdi3_adv + k_acdi3_reg" if prob["dim"] == 3 else
+                        "k_acdi_adv + k_acdi_reg"), "avg_step_us": round(acdi_ms * 1e3, 3),
             "timing": "%d back-to-back ACDI steps between HIP events" % acdi_reps,
             "bytes_per_cell": ab, "achieved": round(ab * ncell / (acdi_ms * 1e-3) / 1e9, 1),
             "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -491,7 +492,7 @@ def main():
         fb = (9 if three else FORCE_WORDS_PER_CELL) * es
         out["config"]["interface_forces"] = True
         out["iface"] = {
-            "kernel": "k_iface3_cells + k_iface3_faces" if three else "k_iface_force",
+            "kernel": "k_iface3_scan + k_iface3_cells + k_iface3_faces" if three else "k_iface_force",
             "avg_launch_us": round(force_ms * 1e3, 3),
             "timing": "%d back-to-back calls between HIP events" % force_reps,
             "bytes_per_cell": fb, "achieved": round(fb * ncell / (force_ms * 1e-3) / 1e9, 1),
@@ -693,8 +694,8 @@ def bench_adjoint(args):
                        "ms_per_step": round(ms_f / N, 6)},
            "adjoint_over_forward_time": round(ms_b / ms_f, 3)}
     ach = bpc * cells / (adj_us * 1e-6) / 1e9
-    kern = ("adjoint step (k_adj_src, k_adj_adv, k_adj_final) on the kept advected state"
-            if star is not None else "adjoint step (k_adv_star, k_adj_src, k_adj_adv, k_adj_final)")
+    kern = ("adjoint step (k_adj3_src, k_adj_adv, k_adj_final) on the kept advected state"
+            if star is not None else "adjoint step (k_adv_star, k_adj3_src, k_adj_adv, k_adj_final)")
     out["roofline"] = {"bound": "hbm", "kernel": kern,
                        "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                        "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None,
