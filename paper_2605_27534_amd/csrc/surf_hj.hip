@@ -16,8 +16,12 @@ void launch_pin(hipStream_t st, dim3 grid, const Grid& g, const Par<R>& p, const
 template <typename R>
 void launch_hj2(hipStream_t st, bool many, const HjArgs<R>& a) {
   const dim3 grid(8 * a.per_xcd), block(256);
-  if (many) hipLaunchKernelGGL((k_hj2<R, 4>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_hj2<R, 1>), grid, block, 0, st, a);
+  // lane offsets within a row: 32 bits reach 4 GiB
+  using W = unsigned long long;
+  const bool wide = (W)a.g.n[0] * sizeof(R) > 0xffffffffull;
+  auto k = many ? (wide ? k_hj2<R, 4, W> : k_hj2<R, 4, unsigned>)
+                : (wide ? k_hj2<R, 1, W> : k_hj2<R, 1, unsigned>);
+  hipLaunchKernelGGL(k, grid, block, 0, st, a);
 }
 
 template <typename R>

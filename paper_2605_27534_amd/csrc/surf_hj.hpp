@@ -144,8 +144,9 @@ struct HjArgs {
 // 1024^2 FP32 and 141 us at 128^2, against 716 and 271 us for one sweep per
 // launch with each linear index divided into coordinates (FP64: 348 against
 // 747 us, 222 against 273).
+// O: the lanes' byte offsets in a row, 32 bits where they reach its end.
 constexpr int HJ2_TY = 16, HJ_LOOKAHEAD = 4;
-template <typename R, int S>
+template <typename R, int S, typename O>
 __global__ void __launch_bounds__(256) k_hj2(HjArgs<R> a) {
   constexpr int OUT = 64 - 2 * S, NY = HJ2_TY + 2 * S;
   const int b = blockIdx.x;
@@ -160,12 +161,12 @@ __global__ void __launch_bounds__(256) k_hj2(HjArgs<R> a) {
   const int xs = x0 - S + lane;
   const int mx = map_axis(xs, nx, g.bc[0][0], g.bc[0][1]);
   const bool out_lane = lane >= S && lane < 64 - S && xs < nx;
-  const int vmx = mx * (int)sizeof(R), vxs = xs * (int)sizeof(R);
+  const O vmx = (O)mx * (O)sizeof(R), vxs = (O)xs * (O)sizeof(R);  // vxs: output lanes only
   R A[S + 1][NY], gv[NY];
   auto load = [&](const int k) {
     const long long row = (long long)nx * map_axis(y0 - S + k, ny, g.bc[1][0], g.bc[1][1]);
-    gv[k] = hj_ld<R>(a.g0 + row, vmx);
-    A[0][k] = hj_ld<R>(a.src + row, vmx);
+    gv[k] = lane_ld<R, O>(a.g0 + row, vmx);
+    A[0][k] = lane_ld<R, O>(a.src + row, vmx);
   };
 #pragma unroll
   for (int k = 0; k < HJ_LOOKAHEAD; ++k) load(k);
@@ -187,7 +188,7 @@ __global__ void __launch_bounds__(256) k_hj2(HjArgs<R> a) {
     if (o >= S && o < NY - S) {
       const int y = y0 - S + o;
       if (out_lane && y < ny)
-        hj_st<R>(HjBits<R>::fold(A[S][o], gv[o]), a.dst + (long long)nx * y, vxs);
+        lane_st<R, O>(HjBits<R>::fold(A[S][o], gv[o]), a.dst + (long long)nx * y, vxs);
     }
   }
 }

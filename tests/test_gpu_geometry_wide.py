@@ -1,0 +1,56 @@
+"""Whole-box redistancing of a 2D box whose rows reach beyond 4 GiB: lane
+offsets within a row that 32 bits do not hold.  Interfaces near the first and
+the last columns; each end equals, bit for bit, a short box that holds the same
+columns (sweeps carry nothing farther than their count)."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+WIN = 600
+
+
+def bands(s, nx, first):
+    """Fractions of a box that starts at column `first` of a row of nx: one
+    band of fluid near each end, ragged by row."""
+    import torch
+    n = s.shape[2]
+    f = torch.zeros(s.shape, dtype=s.dtype, device=s.device)
+    j = torch.arange(4, dtype=s.dtype, device=s.device)[:, None]
+    for c, r in ((60.3, 21.7), (nx - WIN + 250.6, 33.2)):
+        lo = max(int(c) - 60, first)
+        hi = min(int(c) + 60, first + n)
+        if lo >= hi:
+            continue
+        x = torch.arange(lo, hi, dtype=torch.float64, device=s.device)[None, :]
+        f[0, :, lo - first:hi - first] = (0.5 + r + 0.37 * j - (x - c).abs()).clamp(0, 1).to(s.dtype)
+    return f
+
+
+def ends(nx, ny, prec, first, n):
+    """Level set of the first and the last WIN columns after a full build and a
+    warm start, of columns first .. first + n - 1."""
+    import torch
+    from paper_2605_27534_amd import surf as S
+    prob = dict(dim=2, n=(n, ny), h=1e-3, bc=((0, 2), (0, 0)), hj_iters_init=13, hj_iters_step=3)
+    s = S.Surf(prob, 1e-4, prec)
+    f = bands(s, nx, first)
+    s.set_geometry(f, full=True)
+    f.mul_(0.9)
+    s.set_geometry(f, full=False)
+    chi = s.levelset()
+    out = chi[0, :, :WIN].clone(), chi[0, :, -WIN:].clone()
+    torch.cuda.synchronize()
+    s.close()
+    return out
+
+
+def check(nx, prec):
+    import torch
+    left, right = ends(nx, 4, prec, 0, nx)
+    torch.cuda.empty_cache()
+    assert torch.equal(left[:, :400], ends(nx, 4, prec, 0, WIN)[0][:, :400])
+    assert torch.equal(right[:, 100:], ends(nx, 4, prec, nx - WIN, WIN)[1][:, 100:])
+
+
+def test_rows_beyond_4_gib():
+    check(2 ** 29 + 1000, 1)
