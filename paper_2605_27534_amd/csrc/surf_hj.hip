@@ -13,9 +13,14 @@ void launch_pin(hipStream_t st, dim3 grid, const Grid& g, const Par<R>& p, const
     hipLaunchKernelGGL((k_pin<R, 2>), grid, dim3(PIN_TX * PIN_TY), 0, st, g, p, vof, g0, chi);
 }
 
+// n workgroups
+static dim3 hj_grid(int n) {
+  return n <= HJ_GRID_X ? dim3(n) : dim3(HJ_GRID_X, (n + HJ_GRID_X - 1) / HJ_GRID_X);
+}
+
 template <typename R>
 void launch_hj2(hipStream_t st, bool many, const HjArgs<R>& a) {
-  const dim3 grid(8 * a.per_xcd), block(256);
+  const dim3 grid = hj_grid(8 * a.per_xcd), block(256);
   // lane offsets within a row: 32 bits reach 4 GiB
   using W = unsigned long long;
   const bool wide = (W)a.g.n[0] * sizeof(R) > 0xffffffffull;
@@ -26,7 +31,7 @@ void launch_hj2(hipStream_t st, bool many, const HjArgs<R>& a) {
 
 template <typename R>
 void launch_hj3(hipStream_t st, bool many, bool first, const HjArgs<R>& a) {
-  const dim3 grid(8 * a.per_xcd), block(256);
+  const dim3 grid = hj_grid(8 * a.per_xcd), block(256);
   constexpr bool F32 = sizeof(R) == 4;
   const bool off32 = F32 && (unsigned long long)a.g.n[0] * a.g.n[1] * sizeof(R) <= 0xffffffffull;
   auto k = many ? (first ? (off32 ? k_hj3<R, 2, true, F32> : k_hj3<R, 2, true, false>)

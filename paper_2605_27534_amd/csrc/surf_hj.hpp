@@ -136,6 +136,11 @@ struct HjArgs {
   int skip;    // uniform blocks may take the shortcut
 };
 
+// Workgroups along x of a grid that needs more: an axis holds fewer than 2^32
+// threads, which boxes of 4 by 10^9 (2D) and 4 x 4 by 10^8 cells (3D) exceed.
+// A multiple of 8, so that the order over the XCDs stays.
+constexpr int HJ_GRID_X = 1 << 20;
+
 // ---- 2D.  Work unit: one wave, 64 columns and HJ2_TY rows, marching along y.
 // Level l of the sweeps runs l rows behind the loads, on the rows of level
 // l - 1 kept in registers; the x neighbours come from the lanes beside it, so
@@ -149,9 +154,9 @@ constexpr int HJ2_TY = 16, HJ_LOOKAHEAD = 4;
 template <typename R, int S, typename O>
 __global__ void __launch_bounds__(256) k_hj2(HjArgs<R> a) {
   constexpr int OUT = 64 - 2 * S, NY = HJ2_TY + 2 * S;
-  const int b = blockIdx.x;
+  const int b = blockIdx.x + HJ_GRID_X * blockIdx.y;
   const int wg = (b & 7) * a.per_xcd + (b >> 3);
-  if (wg >= a.nwg) return;
+  if ((b >> 3) >= a.per_xcd || wg >= a.nwg) return;
   const Grid& g = a.g;
   const Par<R>& p = a.p;
   const int nx = g.n[0], ny = g.n[1];
@@ -215,7 +220,8 @@ __global__ void __launch_bounds__(256) k_hj3(HjArgs<R> a) {
   // XCD x (workgroups b with b % 8 == x) takes the z blocks x, x + 8, ...:
   // the blocks of a slab share halo rows in its L2, and the slabs that still
   // change, which lie around the interface, spread over all XCDs
-  const int b = blockIdx.x, ygroups = (a.yblocks + 3) / 4, slab = a.strips * ygroups;
+  const int b = blockIdx.x + HJ_GRID_X * blockIdx.y;
+  const int ygroups = (a.yblocks + 3) / 4, slab = a.strips * ygroups;
   const int bz = (b >> 3) / slab * 8 + (b & 7), wg = (b >> 3) % slab;
   if (bz >= a.zblocks) return;
   const Grid& g = a.g;

@@ -1,7 +1,8 @@
-"""Whole-box redistancing of a 2D box whose rows reach beyond 4 GiB: lane
-offsets within a row that 32 bits do not hold.  Interfaces near the first and
-the last columns; each end equals, bit for bit, a short box that holds the same
-columns (sweeps carry nothing farther than their count)."""
+"""Whole-box redistancing of the longest 2D boxes: rows beyond 4 GiB (lane
+offsets within a row that 32 bits do not hold) and more workgroups than one grid
+axis takes.  Interfaces near the first and the last columns; each end equals,
+bit for bit, a short box that holds the same columns (sweeps carry nothing
+farther than their count)."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -54,3 +55,7 @@ def check(nx, prec):
 
 def test_rows_beyond_4_gib():
     check(2 ** 29 + 1000, 1)
+
+
+def test_more_workgroups_than_a_grid_axis():
+    check(945_000_000, 0)
