@@ -574,10 +574,11 @@ int surf_batch_tune(surf_batch* batch, int32_t* choice, double* times_us, int32_
 int surf_batch_destroy(surf_batch* batch);
 
 /* Kernel timing.  While enabled, every launch of the fused transport kernel
- * and of each redistancing sweep is bracketed by HIP events recorded on the
- * context stream.  surf_profile_read waits for the recorded events, returns
- * the summed elapsed milliseconds and launch counts per kind (transport,
- * redistancing) and forgets them.  Any output pointer may be NULL. */
+ * and of the redistancing is bracketed by HIP events recorded on the context
+ * stream.  surf_profile_read waits for the recorded events, returns the summed
+ * elapsed milliseconds and the counts per kind (transport launches; sweeps of
+ * surf_set_geometry, of which a launch holds several, and one for each moving
+ * geometry of a step) and forgets them.  Any output pointer may be NULL. */
 int surf_profile_enable(surf_ctx* ctx, int enable);
 int surf_profile_read(surf_ctx* ctx, double* step_ms, int64_t* step_launches,
                       double* geom_ms, int64_t* geom_launches);

@@ -98,7 +98,7 @@ struct surf_ctx {
   double* adj_part;
   // optional per-launch event timing
   bool profile;
-  struct Mark { hipEvent_t a, b; int kind; };
+  struct Mark { hipEvent_t a, b; int kind, n; };
   std::vector<Mark> marks;
   std::vector<hipEvent_t> pool;
 };
@@ -410,13 +410,15 @@ hipEvent_t take_event(surf_ctx* c) {
   return e;
 }
 
-// brackets one launch with events when profiling is on
+// brackets one launch with events when profiling is on; it counts as n
 struct Timed {
   surf_ctx* c;
   int kind;
   hipStream_t st;
+  int n;
   hipEvent_t a = nullptr, b = nullptr;
-  Timed(surf_ctx* cc, int k, hipStream_t s = nullptr) : c(cc), kind(k), st(s ? s : cc->stream) {
+  Timed(surf_ctx* cc, int k, hipStream_t s = nullptr, int count = 1)
+      : c(cc), kind(k), st(s ? s : cc->stream), n(count) {
     if (c->profile) {
       a = take_event(c);
       b = take_event(c);
@@ -426,7 +428,7 @@ struct Timed {
   ~Timed() {
     if (c->profile && a && b) {
       (void)hipEventRecord(b, st);
-      c->marks.push_back({a, b, kind});
+      c->marks.push_back({a, b, kind, n});
     }
   }
 };
@@ -512,7 +514,7 @@ int geometry_impl(surf_ctx* c, const void* vof, int full) {
     a.fl_in = fl[cur];
     a.fl_out = fl[1 - cur];
     a.fl_init = fl[cur];
-    Timed tm(c, 1);
+    Timed tm(c, 1, nullptr, m ? S : 1);  // counted by sweeps
     if (three) {
       launch_hj3<R>(c->stream, m, k == 0, a);
     } else {
@@ -2847,7 +2849,7 @@ int surf_profile_read(surf_ctx* c, double* step_ms, int64_t* step_n, double* geo
     if (hipEventSynchronize(m.b) != hipSuccess || hipEventElapsedTime(&t, m.a, m.b) != hipSuccess)
       rc = SURF_EDEVICE;
     ms[m.kind] += t;
-    cnt[m.kind] += 1;
+    cnt[m.kind] += m.n;
     c->pool.push_back(m.a);
     c->pool.push_back(m.b);
   }
