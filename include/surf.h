@@ -187,7 +187,8 @@ typedef struct {
   double acdi_zeta;     /* ACDI velocity scale (> 0; the paper takes 1.1
                          * times the largest speed)                      */
   double acdi_vareps;   /* ACDI: s = eps ln((phi + ve)/(1 - phi + ve))
-                         * (0: 1e-6)                                      */
+                         * (0: 1e-6; at least the smallest normal number of
+                         * the precision is taken)                        */
   int32_t limiter;      /* substep 1 slope limiter (section 3.1, BCG face
                          * values): SURF_LIMITER_MINMOD (0) or
                          * SURF_LIMITER_MC, the monotonized central limiter */

@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <limits>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -585,7 +586,9 @@ void acdi_launch(surf_ctx* c, const void* const* u, R* phi_out, R* chi_out,
   a.dt = (R)c->dt;
   a.cfl = (R)(c->dt / c->grid.h);
   a.zeta = (R)c->prm.acdi_zeta;
-  a.ve = (R)c->prm.acdi_vareps;
+  // a normal number: the FP32 quotient and logarithm flush denormals, so that s
+  // would be infinite where phi is 0 or 1
+  a.ve = std::max((R)c->prm.acdi_vareps, std::numeric_limits<R>::min());
   a.ncell = c->ncell;
   a.lim = c->prm.limiter;
   a.tr = c->prm.transverse;

@@ -88,7 +88,8 @@ __device__ __forceinline__ void lane_st(R v, R* base, O off) {
 template <typename R> __device__ __forceinline__ R rexp(R x);
 // exp2 and log2 without the library's scaling of denormal results and
 // arguments: e^x below 2^-126 is 0 here (every use adds it to 1 or to a guard),
-// and every logarithm is of a number of at least 1e-6
+// and every logarithm is of a normal number (at least OM_MIN in the equation
+// of state, ve / (1 + ve) with a normal ve in the ACDI field s)
 template <> __device__ __forceinline__ float rexp<float>(float x) {
   return __builtin_amdgcn_exp2f(x * 1.44269504088896340736f);
 }
