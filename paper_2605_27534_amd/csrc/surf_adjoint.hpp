@@ -443,7 +443,8 @@ __device__ __forceinline__ void adj_select(R s1, R s2, bool& t1, bool& t2) {
 // or wrapped); c and h serve both fields.  Beside a wall or an open side a
 // stencil that reaches one cell past it reaches the side's cell a second time
 // (the cell below of face 1 at the low side, the cell above of face 0 at the
-// high one); the side's own face carries u xi of that cell (open) or nothing,
+// high one), but there the mirrored difference is 0 and minmod takes neither
+// argument; the side's own face carries u xi of that cell (open) or nothing,
 // and the faces beyond do not exist.
 template <typename R, typename O, bool BULK>
 struct AdjAxis {
@@ -534,12 +535,8 @@ struct AdjAxis {
       adj_select<R>(d2, d3, q1, q2);
       auto up = [&](R cc, R h) { return cc + (pick(c1, h) - pick(c2, h)); };
       const R w0 = pick(m2, h0), w3 = -pick(q1, h3);
-      R w1 = p1 ? pick(m2, hf[1]) : up(cf[1], hf[1]);
-      R w2 = p2 ? up(cf[2], hf[2]) : -pick(q1, hf[2]);
-      if (SIDE) {
-        w1 += pick(hi && !p1 && c2, hf[1]);
-        w2 -= pick(lo && p2 && c1, hf[2]);
-      }
+      const R w1 = p1 ? pick(m2, hf[1]) : up(cf[1], hf[1]);
+      const R w2 = p2 ? up(cf[2], hf[2]) : -pick(q1, hf[2]);
       R t1 = w1 * (n[2] - n[1]), t2 = w2 * (n[3] - n[2]);
       if (SIDE) {
         t1 = lo ? pick(openlo, cf[1] * n[2]) : t1;
