@@ -33,9 +33,7 @@
 namespace surf {
 
 constexpr int G3 = 16;                    // tile edge
-constexpr int G3_CELLS = G3 * G3 * G3;    // 4096
 constexpr int G3_THREADS = 256;
-constexpr int G3_CPT = G3_CELLS / G3_THREADS;  // cells per thread (classify)
 
 // live tiles in S's flags: with a cut cell, or all on one side
 enum { G3_CUT = Q_TODO, G3_PLUS = Q_TODO + 1, G3_MINUS = Q_TODO + 2 };

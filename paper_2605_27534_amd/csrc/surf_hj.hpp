@@ -16,20 +16,6 @@
 
 namespace surf {
 
-// Access at a scalar base and a 32-bit lane offset.  The empty statement keeps
-// the offset's widening beside its use: hoisted out of the block, it would
-// turn every access into a 64-bit vector address of its own.
-template <typename R>
-__device__ __forceinline__ R hj_ld(const R* base, unsigned off) {
-  asm("" : "+v"(off));
-  return *(const R*)((const char*)base + off);
-}
-template <typename R>
-__device__ __forceinline__ void hj_st(R v, R* base, unsigned off) {
-  asm("" : "+v"(off));
-  *(R*)((char*)base + off) = v;
-}
-
 template <typename R> struct HjBits;
 template <> struct HjBits<float> {
   static __device__ __forceinline__ float fold(float v, float g) {
@@ -255,7 +241,8 @@ __global__ void __launch_bounds__(256) k_hj3(HjArgs<R> a) {
         for (int z = z0; z < z0 + HJ3_Z && z < nz; ++z)
 #pragma unroll
           for (int y = y0; y < y0 + HJ3_Y; ++y)
-            if (y < ny) hj_st<R>(r, a.dst + (long long)nx * (y + (long long)ny * z), xs * ES);
+            if (y < ny)
+              lane_st<R, unsigned>(r, a.dst + (long long)nx * (y + (long long)ny * z), xs * ES);
       if (lane == 0) {
         a.fl_out[2 * blk] = r;
         a.fl_out[2 * blk + 1] = ms;
@@ -264,7 +251,8 @@ __global__ void __launch_bounds__(256) k_hj3(HjArgs<R> a) {
     }
   }
   const int mx = map_axis(xs, nx, g.bc[0][0], g.bc[0][1]);
-  const int vmx = mx * ES, vxs = xs * ES;
+  // nx < 2^28 (at least 16 rows among 4e9 cells)
+  const unsigned vmx = mx * ES, vxs = xs * ES;
   // OFF32 (FP32, planes of at most 4 GiB): rows take 32-bit byte offsets from the
   // plane; else a pointer each
   unsigned ro[NR], vo[NR];
@@ -281,8 +269,8 @@ __global__ void __launch_bounds__(256) k_hj3(HjArgs<R> a) {
     const R* const sp = a.src + pl;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      gv[k][r] = OFF32 ? hj_ld<R>(gp, vo[r]) : hj_ld<R>(gp + ro[r], vmx);
-      A[0][k][r] = OFF32 ? hj_ld<R>(sp, vo[r]) : hj_ld<R>(sp + ro[r], vmx);
+      gv[k][r] = OFF32 ? lane_ld<R>(gp, vo[r]) : lane_ld<R>(gp + ro[r], vmx);
+      A[0][k][r] = OFF32 ? lane_ld<R>(sp, vo[r]) : lane_ld<R>(sp + ro[r], vmx);
     }
   };
 #pragma unroll
@@ -335,8 +323,8 @@ __global__ void __launch_bounds__(256) k_hj3(HjArgs<R> a) {
         for (int r = S; r < NR - S; ++r) {
           if (y0 - S + r >= ny) break;  // uniform
           // an output lane's column is its own: vo is its offset
-          if (OFF32) hj_st<R>(A[S][o][r], dp, vo[r]);
-          else hj_st<R>(A[S][o][r], dp + ro[r], vxs);
+          if (OFF32) lane_st<R>(A[S][o][r], dp, vo[r]);
+          else lane_st<R>(A[S][o][r], dp + ro[r], vxs);
         }
       }
     }
