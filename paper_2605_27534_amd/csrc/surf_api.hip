@@ -291,15 +291,22 @@ int ntiles_2d(const surf_grid* gr, int* t) {
 // Rows per wave: a wave marches down its rows one after another and computes
 // two more than it owns, so few rows are for boxes that leave the chip idle.
 // 2 while that gives every SIMD at most two waves, 4 while it gives at most
-// four (FP32) or six (FP64), else 8.  With 2, 4, 8 rows the kernel takes (us,
-// with flow)
+// three.  Beyond, 8; but in FP64, where 8 rows just exceed two waves per SIMD and
+// a second round begins, 4 rows up to five.  With 2, 4, 8 rows the kernel alone
+// takes (us, with flow)
 //   FP32  128^2  6.2  7.6 10.7   512^2  8.1  8.5 10.9   733 x 611  9.7  8.9 11.1
 //         1024^2 17.3 15.0 15.2  1500 x 1300 27.6 22.9 22.0
 //   FP64  128^2  7.9 10.2 16.3   512^2 13.9 13.5 16.8   733 x 611 16.2 14.2 19.5
 //         1024^2 32.9 28.4 32.5  1500 x 1300 56.4 46.7 44.2
-// and beside the geometry of the next step, where the rows computed twice cost
-// the other kernel its share, 16 steps at 1024^2 (FP32) take 506 us with 4
-// rows and 477 with 8.
+// and a whole step with 4 and with 8 rows: static, moving, and moving beside the
+// geometry of the next step (8 sweeps), where the rows computed twice cost the
+// other kernel its share
+//   FP32  800^2  16.6 17.7  28.2 29.8  26.0 25.3   900^2  19.4 18.0  31.3 30.1  27.4 27.3
+//         400 x 2000  20.1 19.3  29.7 29.3  26.3 25.6   1500 x 400 16.2 17.9  26.4 28.0  23.2 25.0
+//   FP64  800^2  26.4 29.3  41.4 44.3  36.2 38.0   900^2  32.3 29.8  47.3 45.3  44.0 41.5
+//         1000^2 36.9 40.9  52.1 56.3  48.3 48.9   1100^2 42.7 41.2  62.0 61.4  55.6 52.3
+// Beside a geometry of 16 sweeps 8 rows are 3 to 7% faster in FP32 from 1400 waves
+// of 4 rows on; the launch does not know what runs beside it.
 int col_shape(const surf_grid* gr, const surf_params* p, int* strips, int* groups, int* rows) {
   *strips = *groups = 0;
   *rows = 8;
@@ -309,7 +316,8 @@ int col_shape(const surf_grid* gr, const surf_params* p, int* strips, int* group
   if ((long long)(gr->n[0] + 1) * (gr->n[1] + 1) * es > 0x7fffffffll) return 0;
   *strips = (gr->n[0] + COL_OUT - 1) / COL_OUT;
   auto waves = [&](int r) { return (long long)*strips * ((gr->n[1] + r - 1) / r); };
-  *rows = waves(2) <= 2 * 1024 ? 2 : (waves(4) <= (es == 4 ? 4 : 6) * 1024 ? 4 : 8);
+  const bool second = es == 8 && waves(8) > 2 * 1024 && waves(4) <= 5 * 1024;
+  *rows = waves(2) <= 2 * 1024 ? 2 : (waves(4) <= 3 * 1024 || second ? 4 : 8);
   const int chunks = (gr->n[1] + *rows - 1) / *rows;
   *groups = (chunks + COL_WAVES - 1) / COL_WAVES;
   return *strips * *groups;
