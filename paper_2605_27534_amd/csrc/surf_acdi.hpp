@@ -24,10 +24,11 @@
 // tails s flattens and a unit normal would make that anti-diffusion
 // unbounded; bounded below by 1/2, it is at most zeta eps |grad phi|, and
 // every profile up to twice the equilibrium width keeps the unit normal.
-// Each face flux is evaluated by both of its cells with the same arithmetic
-// in the same order, so the update conserves sum(phi) exactly (in 3D without
-// the substep-1 variants both substeps run in the marching form of
-// surf_acdi3d.hpp).  s is taken of
+// Each face flux is evaluated by both of its cells with the same expressions in
+// the same order, so the update conserves sum(phi) to rounding (the compiler
+// may fuse a flux's last product into either cell's sum).  In 3D without the
+// substep-1 variants both substeps run in the marching form of
+// surf_acdi3d.hpp.  s is taken of
 // phi clamped into [0, 1]; re-initialization from a VoF field (k_acdi_init)
 // sets phi = 1/(1 + e^{chi/eps}) from the level set.  On axisymmetric rings
 // (Appendix B) the fluxes are the same expressions in (r, z), and a radial

@@ -204,7 +204,8 @@ int check_grid_params(const surf_grid* gr, const surf_params* p) {
   if ((p->limiter || p->transverse) && (p->flux_form != SURF_FLUX_WEIGHTED || p->adjoint))
     return SURF_EINVAL;
   // the adjoint kernels index cells and faces in 32 bits and launch a grid of
-  // (nx/64, ny/4, nz) workgroups
+  // (nx/32, ny/8, nz) workgroups, whose y and z hold 65535 (the bound in y is
+  // that of 4 rows a workgroup)
   if (p->adjoint && ((double)(gr->n[0] + 1) * (gr->n[1] + 1) * (gr->n[2] + 1) >= 2147483648.0 ||
                      (gr->n[1] + 3) / 4 > 65535 || gr->n[2] > 65535))
     return SURF_EINVAL;
@@ -388,7 +389,7 @@ int geo3_tiles(const surf_grid* gr, int* t) {
   return t[0] * t[1] * t[2];
 }
 
-// workgroups of the adjoint kernels (64 x 4 cells of one plane each)
+// workgroups of the adjoint kernels (32 x 8 cells of one plane each)
 long long adj_blocks(const surf_grid* gr) {
   return (long long)((gr->n[0] + ADJ_TX - 1) / ADJ_TX) * ((gr->n[1] + ADJ_TY - 1) / ADJ_TY) *
          gr->n[2];

@@ -184,7 +184,7 @@ __global__ void __launch_bounds__(256) k_hj2(HjArgs<R> a) {
   }
 }
 
-// ---- 3D.  Work unit: one wave, a block of 60 x 4 x 8 cells, marching along
+// ---- 3D.  Work unit: one wave, a block of 60 x 4 x 4 cells, marching along
 // z with the block's rows and S halo rows on each side in registers (S = 1
 // or 2 sweeps, level l one plane behind level l - 1).  No LDS, no barrier.
 // A block whose cells all hold one value, with 26 neighbours that hold the
