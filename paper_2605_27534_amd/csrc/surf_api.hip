@@ -492,8 +492,8 @@ int geometry_impl(surf_ctx* c, const void* vof, int full) {
   const int* n = c->g.n;
   const dim3 pg((n[0] + PIN_TX - 1) / PIN_TX, std::min((n[1] + PIN_TY - 1) / PIN_TY, 65535),
                 std::min(n[2], 65535));
-  R* chi0 = full ? (R*)c->chi[c->chi_cur] : nullptr;
-  launch_pin<R>(c->stream, pg, c->g, a.p, f, (R*)c->g0, chi0);
+  R* chi = (R*)c->chi[c->chi_cur];
+  launch_pin<R>(c->stream, pg, c->g, a.p, f, (R*)c->g0, full ? chi : nullptr, full ? nullptr : chi);
   const int iters = full ? hj_init_iters(c) : c->prm.hj_iters_step;
   // the flags of the 3D blocks (two arrays of two numbers each) live in the
   // reduction records, free outside a step: an 80-byte record stands for a

@@ -6,11 +6,9 @@ namespace surf {
 
 template <typename R>
 void launch_pin(hipStream_t st, dim3 grid, const Grid& g, const Par<R>& p, const R* vof, R* g0,
-                R* chi) {
-  if (g.dim == 3)
-    hipLaunchKernelGGL((k_pin<R, 3>), grid, dim3(PIN_TX * PIN_TY), 0, st, g, p, vof, g0, chi);
-  else
-    hipLaunchKernelGGL((k_pin<R, 2>), grid, dim3(PIN_TX * PIN_TY), 0, st, g, p, vof, g0, chi);
+                R* chi, const R* side) {
+  auto k = g.dim == 3 ? k_pin<R, 3> : k_pin<R, 2>;
+  hipLaunchKernelGGL(k, grid, dim3(PIN_TX * PIN_TY), 0, st, g, p, vof, g0, chi, side);
 }
 
 // n workgroups
@@ -42,7 +40,7 @@ void launch_hj3(hipStream_t st, bool many, bool first, const HjArgs<R>& a) {
 }
 
 template void launch_pin<SURF_REAL>(hipStream_t, dim3, const Grid&, const Par<SURF_REAL>&,
-                                    const SURF_REAL*, SURF_REAL*, SURF_REAL*);
+                                    const SURF_REAL*, SURF_REAL*, SURF_REAL*, const SURF_REAL*);
 template void launch_hj2<SURF_REAL>(hipStream_t, bool, const HjArgs<SURF_REAL>&);
 template void launch_hj3<SURF_REAL>(hipStream_t, bool, bool, const HjArgs<SURF_REAL>&);
 

@@ -9,7 +9,9 @@
 // bit of its pin datum).  A cell that is not pinned has six (four)
 // neighbours of its own sign, or it would be cut, so with w the Godunov
 // Hamiltonian has one form for both sides: per axis max(w - w_-, w - w_+, 0),
-// no branch on the sign.
+// no branch on the sign.  A cell whose fraction is NaN is not cut and cuts none
+// of its neighbours; a warm start takes it for the side its level set lies on,
+// since on the other side its neighbours' w would see an interface there.
 #pragma once
 #include "surf_common.hpp"
 #include "surf_col2d.hpp"
@@ -32,7 +34,8 @@ template <> struct HjBits<double> {
 // Pin data: cells whose face neighbour has chi0 = (f - 1/2) h of the opposite
 // (or zero) sign are pinned to the subcell distance h chi0 / Delta
 // (Russo-Smereka); the others carry only the sign of chi0, stored as
-// +-infinity.  chi (a full build) receives chi0.  Workgroups of 64 x 4 cells
+// +-infinity.  chi (a full build) receives chi0; side (a warm start) is the
+// level set, which stands in for a chi0 that is NaN.  Workgroups of 64 x 4 cells
 // of one plane on a (nx/64, ny/4, nz) grid, looping where that exceeds the
 // grid limit: coordinates without divisions (one thread per linear index,
 // which divided twice in 64 bits, took 47 us at 192^3 FP32 beside a separate
@@ -41,7 +44,8 @@ constexpr int PIN_TX = 64, PIN_TY = 4;
 template <typename R, int DIM>
 __global__ void __launch_bounds__(PIN_TX * PIN_TY) k_pin(Grid g, Par<R> p,
                                                         const R* __restrict__ vof,
-                                                        R* __restrict__ g0, R* __restrict__ chi) {
+                                                        R* __restrict__ g0, R* __restrict__ chi,
+                                                        const R* __restrict__ side) {
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const int i = blockIdx.x * PIN_TX + threadIdx.x % PIN_TX;
   if (i >= nx) return;
@@ -52,24 +56,31 @@ __global__ void __launch_bounds__(PIN_TX * PIN_TY) k_pin(Grid g, Par<R> p,
       const long long row = (long long)nx * (j + (long long)ny * k);
       const int jm = map_axis(j - 1, ny, g.bc[1][0], g.bc[1][1]);
       const int jp = map_axis(j + 1, ny, g.bc[1][0], g.bc[1][1]);
-      R nb[2 * DIM];
-      const R fc = vof[row + i];
-      nb[0] = vof[row + im];
-      nb[1] = vof[row + ip];
-      nb[2] = vof[(long long)nx * (jm + (long long)ny * k) + i];
-      nb[3] = vof[(long long)nx * (jp + (long long)ny * k) + i];
+      long long at[2 * DIM];
+      at[0] = row + im;
+      at[1] = row + ip;
+      at[2] = (long long)nx * (jm + (long long)ny * k) + i;
+      at[3] = (long long)nx * (jp + (long long)ny * k) + i;
       if constexpr (DIM == 3) {
         const int km = map_axis(k - 1, nz, g.bc[2][0], g.bc[2][1]);
         const int kp = map_axis(k + 1, nz, g.bc[2][0], g.bc[2][1]);
-        nb[4] = vof[(long long)nx * (j + (long long)ny * km) + i];
-        nb[5] = vof[(long long)nx * (j + (long long)ny * kp) + i];
+        at[4] = (long long)nx * (j + (long long)ny * km) + i;
+        at[5] = (long long)nx * (j + (long long)ny * kp) + i;
       }
-      const R x0 = (fc - R(0.5)) * p.h;
+      R nb[2 * DIM], x0 = (vof[row + i] - R(0.5)) * p.h;
+#pragma unroll
+      for (int d = 0; d < 2 * DIM; ++d) nb[d] = (vof[at[d]] - R(0.5)) * p.h;
+      if (side) {  // uniform
+        if (isnan(x0)) x0 = side[row + i];
+#pragma unroll
+        for (int d = 0; d < 2 * DIM; ++d)
+          if (isnan(nb[d])) nb[d] = side[at[d]];
+      }
       bool cut = false;
       R jump = R(0), grad2 = R(0);
 #pragma unroll
       for (int d = 0; d < DIM; ++d) {
-        const R xm = (nb[2 * d] - R(0.5)) * p.h, xp = (nb[2 * d + 1] - R(0.5)) * p.h;
+        const R xm = nb[2 * d], xp = nb[2 * d + 1];
         cut = cut || (x0 * xm <= R(0)) || (x0 * xp <= R(0));
         jump = fmax(jump, fmax(fabs(xm - x0), fabs(xp - x0)));
         const R cd = R(0.5) * (xp - xm);

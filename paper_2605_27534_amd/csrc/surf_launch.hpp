@@ -21,7 +21,7 @@ template <typename R>
 void launch_col3d(hipStream_t st, const Col3Args<R>& a, bool has_u, bool bulk);
 template <typename R>
 void launch_pin(hipStream_t st, dim3 grid, const Grid& g, const Par<R>& p, const R* vof, R* g0,
-                R* chi);
+                R* chi, const R* side);
 // many: four (2D) or two (3D) sweeps, else one
 template <typename R>
 void launch_hj2(hipStream_t st, bool many, const HjArgs<R>& a);

@@ -923,6 +923,7 @@ __global__ void __launch_bounds__(GEO_WG) k_geo_live(Step2dArgs<R> a) {
 #pragma unroll
     for (int it = 0; it < IC; ++it) {
       rv[it] = (rv[it] - R(0.5)) * p.h;
+      rv[it] = isnan(rv[it]) ? cur[it] : rv[it];  // a NaN fraction: the side of the level set
       if (cl[it] < NC) sB[cl[it]] = rv[it];
     }
     __syncthreads();
