@@ -215,14 +215,17 @@ __global__ void __launch_bounds__(G3_THREADS) k_geo3_classify(Geo3Args ga, Par<R
       anycut = anycut | (cut & colin & (z0 + k < nz));
     }
   }
-  const bool wc = __any(anycut);
+  // without a cut cell the tile lies on one side, that of any of its cells but
+  // those whose fraction is NaN
+  const bool wc = __any(anycut), wp = __any(colin & (f[0] > R(0)));
   __syncthreads();  // the first vote has been read
-  if ((tid & 63) == 0) sVote[tid >> 6] = wc ? 1 : 0;
+  if ((tid & 63) == 0) sVote[tid >> 6] = (wc ? 1 : 0) | (wp ? 2 : 0);
   __syncthreads();
-  int cuts = 0;
+  int votes = 0;
 #pragma unroll
-  for (int w = 0; w < G3_THREADS / 64; ++w) cuts |= sVote[w];
-  if (tid == 0) q_out[t] = (uint8_t)(cuts ? G3_CUT : (f[0] > R(0) ? G3_PLUS : G3_MINUS));
+  for (int w = 0; w < G3_THREADS / 64; ++w) votes |= sVote[w];
+  const bool cuts = votes & 1;
+  if (tid == 0) q_out[t] = (uint8_t)(cuts ? G3_CUT : ((votes & 2) ? G3_PLUS : G3_MINUS));
   if (!cuts) return;  // the code says what every pin datum of the tile is
   R* const gz0 = g0 + pl * z0;
 #pragma unroll

@@ -1,7 +1,7 @@
 """A NaN among the fractions given to a warm start, two cells or more from the
 interface: the level set is that of the clean fractions (the cell is taken for
-the side its level set lies on), on the whole box and in the moving geometry of
-the 2D steps.  Tolerances as in test_gpu_geometry_build: 1e-12 and 2e-5 of the
+the side its level set lies on), on the whole box, in the moving geometry of the
+2D steps, and in that of the 3D steps in a tile without a cut cell.  Tolerances as in test_gpu_geometry_build: 1e-12 and 2e-5 of the
 clamp."""
 import numpy as np
 import pytest
@@ -24,6 +24,9 @@ CASES = [
     ((30, 28), ((W, W), (P, P)), 3, ((15, 14), (29, 0)), True),
     ((36, 34, 40), ((P, P), (OP, W), (P, P)), 4, ((18, 17, 20), (35, 0, 39)), False),
     ((30, 28, 26), ((W, W), (P, P), (OP, OP)), 5, ((15, 13, 14), (1, 27, 2)), True),
+    # the first cell of the tile of 16^3 in the middle of a ball, and another
+    ((80, 80, 80), ((W, W), (P, P), (OP, OP)), 4, ((32, 32, 32),), True),
+    ((80, 80, 80), ((P, P), (W, W), (OP, OP)), 4, ((41, 36, 46), (5, 5, 5)), True),
 ]
 
 
